@@ -10,6 +10,9 @@
 // the entries within a Hamming radius of its signature (radius 0 is equality
 // of hash keys), found by one pass over the signatures (bits / 8 bytes per
 // entry instead of the key's d * 2), and re-ranked by their exact similarity.
+#include <type_traits>
+#include <utility>
+
 #include "verify.hpp"
 
 namespace lacache {
@@ -18,71 +21,223 @@ namespace {
 constexpr int kScanQueries = 1024;  // query signatures held in LDS per scan launch
 }
 
-// Copy a row-major [rows][d] bfloat16 matrix into the tiled layout with d_pad columns (zero padded), as is.
-__global__ __launch_bounds__(256) void k_tile_rows(const uint16_t* __restrict__ src, int rows, int d, int d_pad,
-                                                   uint16_t* __restrict__ dst) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (int64_t)rows * d_pad) return;
-    const int r = (int)(t / d_pad), c = (int)(t - (int64_t)r * d_pad);
-    dst[tiled_offset(r, c, d_pad >> 5)] = c < d ? src[(int64_t)r * d + c] : (uint16_t)0;
+// ---------------------------------------------------------------------------
+// Signature bits on the matrix cores.  The hyperplanes are the row operand of
+// v_mfma_f32_16x16x32_bf16 and the vectors the column operand, so lane l ends
+// with the projections of vector l % 16 on rows 4 q .. 4 q + 3 (q = l / 16) of
+// each 16-hyperplane block.  The hyperplanes are stored in the order that
+// makes those bits land where the signature keeps them: with W words (2 W
+// blocks), row 4 q + i of block hb is hyperplane 8 W q + 4 hb + i, so over all
+// blocks lane q of a vector collects bytes W q .. W q + W - 1 of its 4 W
+// signature bytes in order and stores them without any exchange.
+// ---------------------------------------------------------------------------
+
+// The lane index computed afresh (not kept live across a main loop whose registers are all in use).
+__device__ inline int fresh_lane() {
+    int r;
+    __asm__ volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(r));
+    return r;
 }
 
-// One wave per (16-row group of a tiled matrix, run of `wpw` signature words): the projections of its rows on
-// the hyperplanes of those words (16 at a time, v_mfma_f32_16x16x32_bf16 with the rows as the row operand; the
-// two 16-hyperplane halves of a word accumulate side by side), packed into sign bits.  Lane l holds, for
-// hyperplane 16 hg + l % 16, the rows 4 (l / 16) + j (j = 0..3); a ballot per j gathers the 16 bits of each
-// row.  Rows outside [row0, row0 + n) are not written.  Grid-stride over the waves.
-__global__ __launch_bounds__(256) void k_simhash(const u32x4* __restrict__ rows_tiled, int kc, int64_t row0,
-                                                 int64_t n, const u32x4* __restrict__ hp_tiled, int bits, int wpw,
-                                                 uint32_t* __restrict__ sig) {
+// f(0), f(1), ... with compile-time indices.
+template <int... Q, class F>
+__device__ __forceinline__ void for_each_index(std::integer_sequence<int, Q...>, F f) {
+    (f(std::integral_constant<int, Q>{}), ...);
+}
+
+// Hyperplane held by row p of the tiled hyperplane matrix.
+__host__ __device__ inline int hyperplane_at(int p, int words) {
+    return 8 * words * ((p >> 2) & 3) + 4 * (p >> 4) + (p & 3);
+}
+
+// x shifted left by one with the sign bit of f + 0 shifted in (f + 0: a negative zero counts as >= 0).
+__device__ inline uint32_t push_sign(uint32_t x, float f) {
+    return __builtin_amdgcn_alignbit(x, __float_as_uint(f + 0.0f), 31);
+}
+
+// The 4 bits (projection >= 0) of block accumulator `lo` in bits 0..3 and of `hi` in bits 4..7.
+__device__ inline uint32_t sign_byte(f32x4 lo, f32x4 hi) {
+    uint32_t x = 0u;
+#pragma unroll
+    for (int i = 3; i >= 0; --i) x = push_sign(x, hi[i]);
+#pragma unroll
+    for (int i = 3; i >= 0; --i) x = push_sign(x, lo[i]);
+    return ~x & 0xFFu;
+}
+
+// The [32 words][d] row-major bfloat16 hyperplanes as a tiled matrix of d_pad columns (zero padded), its rows in
+// the order above.
+__global__ __launch_bounds__(256) void k_tile_hyperplanes(const uint16_t* __restrict__ src, int words, int d,
+                                                          int d_pad, uint16_t* __restrict__ dst) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= (int64_t)words * 32 * d_pad) return;
+    const int p = (int)(t / d_pad), c = (int)(t - (int64_t)p * d_pad);
+    dst[tiled_offset(p, c, d_pad >> 5)] = c < d ? src[(int64_t)hyperplane_at(p, words) * d + c] : (uint16_t)0;
+}
+
+// Signatures of many rows (building the index, bulk inserts).  The projection of N rows on 32 W hyperplanes is a
+// [N][d] x [d][32 W] product of which only the signs are kept: at 256 bits 512 FLOP per 2 key bytes, about the
+// balance of the matrix cores and HBM, so both have to stream.  A workgroup is four waves, one per SIMD (two
+// workgroups per CU up to 96 bits); a wave multiplies 64 rows by all HB = 2 W hyperplane blocks, so every row is
+// read once, straight from memory into operand registers, SETS - 1 steps of 32 columns ahead (what the launch
+// holds in flight is what bounds its bandwidth).  The hyperplanes, which every wave needs, pass through LDS in
+// two slots of two steps each; a part's fragments (PARTS = 2: half of the blocks) are read while the part before
+// it multiplies, which needs one LDS barrier per two steps: after it the slot just drained is refilled.
+// 1M x 768 rows: 345 us at 256 bits (1.14 PFLOP/s, rows at 4.5 TB/s), 263 us at 128, 239 us at 64 (6.4 TB/s).
+// One wave per 16 rows with both operands from L2 took 1790 us at 256 bits; 128-row x 128-hyperplane waves that
+// read every row twice 386 us.
+template <int HB, int PARTS, int SETS>
+__global__ __launch_bounds__(256, HB <= 6 ? 2 : 1) void k_simhash_bulk(const u32x4* __restrict__ rows_tiled, int kc,
+                                                                       int64_t row0, int64_t n,
+                                                                       const u32x4* __restrict__ hp_tiled,
+                                                                       int n_tiles, uint8_t* __restrict__ sig) {
+    constexpr int kRB = 4;                  // 16-row blocks per wave
+    constexpr int kHP = HB / PARTS;         // hyperplane blocks per part of a step
+    constexpr int kWaves = 4, kBytes = 2 * HB;  // signature bytes of a row
+    constexpr int kTile = kWaves * kRB;     // 16-row groups per workgroup tile
+    constexpr int kSteps = 2;               // 32-column steps per LDS slot
+    constexpr int kSlot = kSteps * HB;      // 1 KiB chunks per slot
+    constexpr int kMine = kSlot / kWaves;   // chunks a wave stages per slot
+    static_assert(kSlot % kWaves == 0 && SETS % 4 == 0, "");
+    __shared__ u32x4 ring[2 * kSlot * 64];
     const int lane = threadIdx.x & 63;
-    const int words = bits >> 5;
-    const int chunks = words / wpw;  // word runs per group
-    // grid-stride over the waves; groups grow with the wave index, so the first one past the rows ends the loop
-    for (int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);; wave += (int64_t)gridDim.x * 4) {
-        const int64_t g = (row0 >> 4) + wave / chunks;  // 16-row group
-        const int w0 = (int)(wave % chunks) * wpw;
-        if (g * 16 >= row0 + n) break;
-        const u32x4* a = rows_tiled + g * kc * 64 + lane;
-        for (int w = w0; w < w0 + wpw; ++w) {
-            f32x4 lo = f32x4{0.f, 0.f, 0.f, 0.f}, hi = f32x4{0.f, 0.f, 0.f, 0.f};
-            const u32x4* b0 = hp_tiled + (int64_t)(2 * w) * kc * 64 + lane;
-            const u32x4* b1 = b0 + (int64_t)kc * 64;
-            for (int c = 0; c < kc; c += 4) {  // kc is a multiple of 4: twelve loads in flight per step
-                u32x4 x[4], y0[4], y1[4];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = (int)((int64_t)blockIdx.x * n_tiles / gridDim.x);
+    const int t1 = (int)((int64_t)(blockIdx.x + 1) * n_tiles / gridDim.x);
+    const int64_t g0 = row0 >> 4;
+    const uint32_t lane16 = (uint32_t)lane * 16;
+
+    // rows: chunk (block kb, step j) of the wave's part of a tile at byte (kb * kc + j) * 1024 from the tile's
+    // base.  A tile reads at most 511 rows past the call's last one, fewer than the store's 512 spare rows.  The
+    // loads run SETS - 1 steps ahead into the next tile; in the last tile they start over, and are not used.
+    const char* kbase = (const char*)(rows_tiled + (g0 + (int64_t)t0 * kTile + wv * kRB) * kc * 64);
+    const int tile_bytes = kTile * kc * 1024;
+    __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)kbase, 0, 0x7FFFFFFF, 0x00020000);
+    int kstep = 0, koff = 0, wrap = (t0 + 1 < t1 ? tile_bytes : 0) - kc * 1024;
+    u32x4 kf[SETS][kRB];
+    auto rows_load = [&](u32x4 (&dst)[kRB]) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    x[u] = a[(c + u) * 64];
-                    y0[u] = b0[(c + u) * 64];
-                    y1[u] = b1[(c + u) * 64];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    lo = mfma16x16x32(x[u], y0[u], lo);
-                    hi = mfma16x16x32(x[u], y1[u], hi);
-                }
-            }
-            uint32_t word = 0u;
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const f32x4 acc = half ? hi : lo;
-                uint64_t m[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) m[j] = __ballot(acc[j] >= 0.0f);
-                // lane l < 16 owns row 4 (l / 4) + l % 4 = l of the group: its bits sit in m[l % 4] at 16 (l / 4)
-                const uint64_t mine =
-                    (lane & 3) == 0 ? m[0] : (lane & 3) == 1 ? m[1] : (lane & 3) == 2 ? m[2] : m[3];
-                word |= ((uint32_t)(mine >> (16 * ((lane >> 2) & 3))) & 0xFFFFu) << (16 * half);
-            }
-            const int64_t row = g * 16 + lane;
-            if (lane < 16 && row >= row0 && row < row0 + n) sig[row * words + w] = word;
+        for (int kb = 0; kb < kRB; ++kb)  // read once: non-temporal
+            dst[kb] = __builtin_amdgcn_raw_buffer_load_b128(krs, lane16, koff + kb * kc * 1024, 2);
+        koff += 1024;
+        if (++kstep == kc) {
+            kstep = 0;
+            koff += wrap;
         }
+    };
+
+    // hyperplanes: chunk c = s * HB + hb of a slot is block hb at its step s; wave wv stages chunks wv, wv + 4, ...
+    const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)hp_tiled, 0, 0x7FFFFFFF, 0x00020000);
+    u32x4 sr[kMine];
+    int ld_step = 0;
+    auto slot_load = [&]() {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            const int c = wv + kWaves * i;
+            sr[i] = __builtin_amdgcn_raw_buffer_load_b128(hrs, lane16, ((c % HB) * kc + c / HB + ld_step) * 1024, 0);
+        }
+        ld_step += kSteps;
+        if (ld_step == kc) ld_step = 0;
+    };
+    auto slot_store = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) ring[(slot * kSlot + wv + kWaves * i) * 64 + lane] = sr[i];
+    };
+    u32x4 hf[2][kHP];
+    auto frags = [&](int slot, int s, int p, u32x4 (&dst)[kHP]) {
+#pragma unroll
+        for (int hb = 0; hb < kHP; ++hb) dst[hb] = ring[(slot * kSlot + s * HB + p * kHP + hb) * 64 + lane];
+    };
+    auto barrier = [&]() {  // orders LDS accesses only: loads from memory stay in flight across it
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+
+    f32x4 acc[kRB][HB];
+#pragma unroll
+    for (int p = 0; p < SETS - 1; ++p) rows_load(kf[p]);
+    slot_load();
+    slot_store(0);
+    slot_load();
+    slot_store(1);
+    slot_load();
+    barrier();
+    frags(0, 0, 0, hf[0]);
+
+    // one part of a step: load the rows SETS - 1 steps ahead, read the next part's fragments, multiply set u (the
+    // row loads spread between the multiplications: bursts of loads stall the wave's issue)
+    auto part = [&](auto q_tag, bool zero) {
+        constexpr int q = decltype(q_tag)::value, u = q / PARTS, p = q % PARTS;
+        constexpr int v = (q + 1) % (SETS * PARTS), vu = v / PARTS % 4;  // the next part, its step
+        if constexpr (u % 2 == 1 && p == PARTS - 1) {
+            barrier();
+            slot_store(u / 2 % 2);
+            slot_load();
+        }
+        if constexpr (p == 0) rows_load(kf[(u + SETS - 1) % SETS]);
+        frags(vu >> 1, vu & 1, v % PARTS, hf[v & 1]);
+#pragma unroll
+        for (int kb = 0; kb < kRB; ++kb)
+#pragma unroll
+            for (int hb = 0; hb < kHP; ++hb) {
+                f32x4& c = acc[kb][p * kHP + hb];
+                c = mfma16x16x32(hf[q & 1][hb], kf[u][kb], zero ? f32x4{} : c);
+            }
+#pragma unroll
+        for (int i = 0; i < kRB; ++i) {
+            if (p == 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
+            __builtin_amdgcn_sched_group_barrier(0x008, kHP, 0);            // MFMA
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto body = [&](auto first_tag) {
+        constexpr bool first = decltype(first_tag)::value;
+        for_each_index(std::make_integer_sequence<int, SETS * PARTS>{},
+                       [&](auto q) { part(q, first && decltype(q)::value < PARTS); });
+    };
+
+    for (int t = t0; t < t1; ++t) {
+        wrap = (t + 1 < t1 ? tile_bytes : 0) - kc * 1024;
+        body(std::true_type{});
+        for (int j = SETS; j < kc; j += SETS) body(std::false_type{});
+        // the lane's 4 HB bits of each row, collected from the top down; rel is the row within the call
+        const int ln = fresh_lane();
+        const int rel0 = (t * kTile + wv * kRB) * 16 - (int)(row0 & 15) + (ln & 15);
+        uint8_t* const dst0 = sig + row0 * kBytes + (ln >> 4) * (HB / 2);
+#pragma unroll
+        for (int kb = 0; kb < kRB; ++kb) {
+            uint32_t x[2] = {0u, 0u};
+#pragma unroll
+            for (int hb = HB - 1; hb >= 0; --hb)
+#pragma unroll
+                for (int i = 3; i >= 0; --i) x[hb >> 3] = push_sign(x[hb >> 3], acc[kb][hb][i]);
+            const int rel = rel0 + kb * 16;
+            if (rel >= 0 && rel < n) {
+                uint8_t* dst = dst0 + (int64_t)rel * kBytes;
+                if constexpr (HB == 16) {
+                    *(uint2*)dst = uint2{~x[0], ~x[1]};
+                } else if constexpr (HB == 8) {
+                    *(uint32_t*)dst = ~x[0];
+                } else if constexpr (HB == 4) {
+                    *(uint16_t*)dst = (uint16_t)~x[0];
+                } else {
+#pragma unroll
+                    for (int y = 0; y < HB / 2; ++y) dst[y] = (uint8_t)(~x[y >> 2] >> (8 * (y & 3)));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        kbase += tile_bytes;
+        koff -= tile_bytes;
+        krs = __builtin_amdgcn_make_buffer_rsrc((void*)kbase, 0, 0x7FFFFFFF, 0x00020000);
     }
 }
 
-// Signature word of 16 rounded queries against hyperplanes b0 (bits 0..15 of the word) and b1 (16..31): S
+// One signature byte per lane: blocks b0 (bits 0..3) and b1 (bits 4..7) of the hyperplanes against 16 vectors, S
 // column chunks c0 .. c0+S-1, every operand load of the batch issued before its first MFMA.  xat(c) gives the
-// lane's piece of query chunk c.
+// lane's piece of vector chunk c.
 template <int S, class X>
 __device__ __forceinline__ void simhash_batch(X xat, const u32x4* __restrict__ b0, const u32x4* __restrict__ b1,
                                               int c0, f32x4& lo, f32x4& hi) {
@@ -96,15 +251,46 @@ __device__ __forceinline__ void simhash_batch(X xat, const u32x4* __restrict__ b
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < S; ++u) {
-        lo = mfma16x16x32(x[u], y0[u], lo);
-        hi = mfma16x16x32(x[u], y1[u], hi);
+        lo = mfma16x16x32(y0[u], x[u], lo);
+        hi = mfma16x16x32(y1[u], x[u], hi);
+    }
+}
+
+// Byte `wv` (0 .. words-1) of every lane's signature bytes for 16 vectors of kc chunks.
+template <class X>
+__device__ __forceinline__ uint32_t simhash_byte(X xat, const u32x4* __restrict__ hp_tiled, int kc, int wv, int lane) {
+    const u32x4* b0 = hp_tiled + (int64_t)(2 * wv) * kc * 64 + lane;
+    const u32x4* b1 = b0 + (int64_t)kc * 64;
+    f32x4 lo = f32x4{0.f, 0.f, 0.f, 0.f}, hi = f32x4{0.f, 0.f, 0.f, 0.f};
+    int c = 0;
+    for (; c + 8 <= kc; c += 8) simhash_batch<8>(xat, b0, b1, c, lo, hi);
+    if (c < kc) simhash_batch<4>(xat, b0, b1, c, lo, hi);  // kc is a multiple of 4
+    return sign_byte(lo, hi);
+}
+
+// Signatures of few rows (an insert of some hundred entries): one wave per (16-row group, signature byte of
+// every lane), so that the blocks of a group are computed in parallel.  Rows outside [row0, row0 + n) are not
+// written.  Grid-stride over the waves.
+__global__ __launch_bounds__(256) void k_simhash_few(const u32x4* __restrict__ rows_tiled, int kc, int64_t row0,
+                                                     int64_t n, const u32x4* __restrict__ hp_tiled, int words,
+                                                     uint8_t* __restrict__ sig) {
+    const int lane = threadIdx.x & 63;
+    // groups grow with the wave index, so the first one past the rows ends the loop
+    for (int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);; wave += (int64_t)gridDim.x * 4) {
+        const int64_t g = (row0 >> 4) + wave / words;
+        const int wv = (int)(wave % words);
+        if (g * 16 >= row0 + n) break;
+        const u32x4* a = rows_tiled + g * kc * 64 + lane;
+        const uint32_t byte = simhash_byte([&](int c) { return a[c * 64]; }, hp_tiled, kc, wv, lane);
+        const int64_t row = g * 16 + (lane & 15);
+        if (row >= row0 && row < row0 + n) sig[row * (4 * words) + (lane >> 4) * words + wv] = (uint8_t)byte;
     }
 }
 
 // Query preparation for the LSH lookup, one workgroup of 16 waves per 16 queries: wave w normalises and
 // rounds query 16 g + w into the tiled scratch exactly as stored vectors are (zeros past the batch) and
-// clears its candidate count; after the barrier wave w < bits / 32 computes signature word w of the 16
-// queries with the MFMA sequence of k_simhash (so a query equal to a stored key gets its signature).
+// clears its candidate count; after the barrier wave w < bits / 32 computes byte w of every lane's part of the
+// signatures with the MFMA sequence of the stored rows (so a query equal to a stored key gets its signature).
 // NC > 0 (d_pad <= 512 NC): the query row is read once into registers, and the rounded queries are also
 // kept in LDS (the tiled chunk layout), where the signature MFMAs read them; the hyperplane chunks are
 // loaded eight at a time.  NC = 0: any d, the rows read twice and the queries read back from the scratch.
@@ -143,25 +329,10 @@ __global__ __launch_bounds__(1024) void k_lsh_prep(const void* __restrict__ quer
     const int words = bits >> 5;
     if (wv >= words) return;
     const u32x4* a = (const u32x4*)qt + (int64_t)g * kc * 64 + lane;
-    const u32x4* b0 = hp_tiled + (int64_t)(2 * wv) * kc * 64 + lane;
-    const u32x4* b1 = b0 + (int64_t)kc * 64;
-    f32x4 lo = f32x4{0.f, 0.f, 0.f, 0.f}, hi = f32x4{0.f, 0.f, 0.f, 0.f};
     auto xat = [&](int c) { return NC > 0 ? qs[c * 64 + lane] : a[c * 64]; };
-    int c = 0;
-    for (; c + 8 <= kc; c += 8) simhash_batch<8>(xat, b0, b1, c, lo, hi);
-    if (c < kc) simhash_batch<4>(xat, b0, b1, c, lo, hi);  // kc is a multiple of 4
-    uint32_t word = 0u;
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const f32x4 acc = half ? hi : lo;
-        uint64_t m[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) m[j] = __ballot(acc[j] >= 0.0f);
-        const uint64_t mine = (lane & 3) == 0 ? m[0] : (lane & 3) == 1 ? m[1] : (lane & 3) == 2 ? m[2] : m[3];
-        word |= ((uint32_t)(mine >> (16 * ((lane >> 2) & 3))) & 0xFFFFu) << (16 * half);
-    }
-    const int row = g * 16 + lane;
-    if (lane < 16 && row < nb) sigq[(int64_t)row * words + wv] = word;
+    const uint32_t byte = simhash_byte(xat, hp_tiled, kc, wv, lane);
+    const int row = g * 16 + (lane & 15);
+    if (row < nb) ((uint8_t*)sigq)[(int64_t)row * (4 * words) + (lane >> 4) * words + wv] = (uint8_t)byte;
 }
 
 // Candidates of queries q0 .. q0+nq-1: every entry whose signature differs from the query's in at most `radius`
@@ -252,24 +423,56 @@ __global__ __launch_bounds__(256) void k_lsh_verify(const u32x4* __restrict__ ke
                  idx_out, score_out, resp_out, dec_out, lane);
 }
 
-hipError_t launch_tile_rows(const uint16_t* src, int rows, int d, int d_pad, uint16_t* dst, hipStream_t s) {
-    const int64_t total = (int64_t)rows * d_pad;
+hipError_t launch_tile_hyperplanes(const uint16_t* src, int bits, int d, int d_pad, uint16_t* dst, hipStream_t s) {
+    const int64_t total = (int64_t)bits * d_pad;
     if (total <= 0) return hipSuccess;
-    k_tile_rows<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(src, rows, d, d_pad, dst);
+    k_tile_hyperplanes<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(src, bits >> 5, d, d_pad, dst);
     return hipGetLastError();
 }
 
+template <int HB, int PARTS, int SETS>
+static void launch_bulk(const uint16_t* rows_tiled, int kc, int64_t row0, int64_t n, const uint16_t* hp_tiled,
+                        uint32_t* sig, int num_cu, hipStream_t s) {
+    const int64_t groups = ((row0 + n + 15) >> 4) - (row0 >> 4);
+    const int n_tiles = (int)((groups + 15) / 16);
+    const int cap = HB <= 6 ? 2 * num_cu : num_cu;  // the workgroups that the registers allow at once
+    k_simhash_bulk<HB, PARTS, SETS><<<dim3(n_tiles < cap ? n_tiles : cap), dim3(256), 0, s>>>(
+        (const u32x4*)rows_tiled, kc, row0, n, (const u32x4*)hp_tiled, n_tiles, (uint8_t*)sig);
+}
+
+// Rows per call up to which a wave per (16-row group, block pair) is used.  It spreads a call over the whole chip
+// but reads the hyperplanes once per group; a bulk call lasts at least one tile's chain (20 us at 768 columns).
+// Measured, few / bulk, us: 256 bits x 768 columns 8.2 / 20 at 4096 rows, 14 / 20 at 8192, 23 / 20 at 16384,
+// 112 / 31 at 65536; 128 bits x 1024 columns 6.9 / 24, 9.9 / 25, 16 / 24, 85 / 35.
+constexpr int64_t kFewRows = 8192;
+
 hipError_t launch_simhash(const uint16_t* rows_tiled, int d_pad, int64_t row0, int64_t n, const uint16_t* hp_tiled,
-                          int bits, uint32_t* sig, hipStream_t s) {
+                          int bits, uint32_t* sig, int num_cu, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const int64_t g0 = row0 >> 4, g1 = (row0 + n + 15) >> 4;
-    const int words = bits >> 5;
-    // few rows (a query batch): one wave per signature word, so the words of a group are computed in parallel;
-    // many rows (building the index): one wave per group, reading its rows once for every word
-    const int wpw = (g1 - g0) * words <= 4096 ? 1 : words;
-    const int64_t waves = (g1 - g0) * (words / wpw);
-    k_simhash<<<dim3((unsigned)grid_blocks((waves + 3) / 4)), dim3(256), 0, s>>>(
-        (const u32x4*)rows_tiled, d_pad >> 5, row0, n, (const u32x4*)hp_tiled, bits, wpw, sig);
+    const int words = bits >> 5, kc = d_pad >> 5;
+    if (n <= kFewRows) {
+        const int64_t groups = ((row0 + n + 15) >> 4) - (row0 >> 4);
+        k_simhash_few<<<dim3((unsigned)grid_blocks((groups * words + 3) / 4)), dim3(256), 0, s>>>(
+            (const u32x4*)rows_tiled, kc, row0, n, (const u32x4*)hp_tiled, words, (uint8_t*)sig);
+        return hipGetLastError();
+    }
+    // d_pad % 256 == 0: whole groups of 8 steps, so the rows are loaded 7 steps ahead where the registers allow
+    // (1M x 768 rows, 256 bits: 345 us against 367 us three steps ahead)
+    const bool deep = kc % 8 == 0;
+    auto run = [&](auto shallow, auto deeper) {
+        (deep ? deeper : shallow)(rows_tiled, kc, row0, n, hp_tiled, sig, num_cu, s);
+    };
+    switch (words) {
+        case 1: run(launch_bulk<2, 1, 4>, launch_bulk<2, 1, 4>); break;
+        case 2: run(launch_bulk<4, 1, 4>, launch_bulk<4, 1, 4>); break;
+        case 3: run(launch_bulk<6, 1, 4>, launch_bulk<6, 1, 4>); break;
+        case 4: run(launch_bulk<8, 1, 4>, launch_bulk<8, 1, 8>); break;
+        case 5: run(launch_bulk<10, 2, 4>, launch_bulk<10, 2, 8>); break;
+        case 6: run(launch_bulk<12, 2, 4>, launch_bulk<12, 2, 8>); break;
+        case 7: run(launch_bulk<14, 2, 4>, launch_bulk<14, 2, 8>); break;
+        case 8: run(launch_bulk<16, 2, 4>, launch_bulk<16, 2, 8>); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -254,7 +254,7 @@ int lacache_insert_ensemble(lacache_t h, const void* keys, const void* const* re
     if (hipMemcpyAsync(h->tokens + first * h->k_cap, resp_tokens, (size_t)n * h->k_cap * 4,
                        hipMemcpyDeviceToDevice, s) != hipSuccess)
         return LACACHE_EHIP;
-    if (h->lsh_bits && launch_simhash(h->keys, h->d_pad, first, n, h->hp, h->lsh_bits, h->sig, s) != hipSuccess)
+    if (h->lsh_bits && launch_simhash(h->keys, h->d_pad, first, n, h->hp, h->lsh_bits, h->sig, h->num_cu, s) != hipSuccess)
         return LACACHE_EHIP;
     h->size += n;
     if (first_idx) *first_idx = first;
@@ -445,8 +445,8 @@ int lacache_enable_lsh(lacache_t h, int32_t bits, const uint16_t* hyperplanes, i
     }
     h->lsh_bits = bits;
     h->lsh_max_cand = max_candidates;
-    if (launch_tile_rows(hyperplanes, bits, h->d, h->d_pad, h->hp, s) != hipSuccess ||
-        launch_simhash(h->keys, h->d_pad, 0, h->size, h->hp, bits, h->sig, s) != hipSuccess)
+    if (launch_tile_hyperplanes(hyperplanes, bits, h->d, h->d_pad, h->hp, s) != hipSuccess ||
+        launch_simhash(h->keys, h->d_pad, 0, h->size, h->hp, bits, h->sig, h->num_cu, s) != hipSuccess)
         return LACACHE_EHIP;
     return LACACHE_OK;
 }

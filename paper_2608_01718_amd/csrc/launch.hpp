@@ -118,13 +118,14 @@ hipError_t calibrate_static_scratch(uint32_t** out);
 hipError_t launch_accept_length(const void* logits, int dtype, int V, const int32_t* tokens, const float* p_draft,
                                 int B, int k, int32_t* accept_len, float* p_target, hipStream_t s);
 
-// LSH index (random hyperplanes): tiled copy of the raw hyperplanes, signatures of rows row0 .. row0+n-1 of a
+// LSH index (random hyperplanes): tiled copy of the raw hyperplanes (their rows in the order the signature
+// kernels want), signatures of rows row0 .. row0+n-1 of a
 // tiled matrix ([rows][bits / 32] words, bit i of a row is 1 when its projection on hyperplane i is >= 0),
 // and the whole LSH lookup of a query batch (query preparation, Hamming-radius candidate scan, exact re-rank,
 // threshold and stage 2).
-hipError_t launch_tile_rows(const uint16_t* src, int rows, int d, int d_pad, uint16_t* dst, hipStream_t s);
+hipError_t launch_tile_hyperplanes(const uint16_t* src, int bits, int d, int d_pad, uint16_t* dst, hipStream_t s);
 hipError_t launch_simhash(const uint16_t* rows_tiled, int d_pad, int64_t row0, int64_t n, const uint16_t* hp_tiled,
-                          int bits, uint32_t* sig, hipStream_t s);
+                          int bits, uint32_t* sig, int num_cu, hipStream_t s);
 hipError_t launch_lsh_lookup(const void* queries, int dtype, int nb, int d, int d_pad, uint16_t* qt,
                              const uint16_t* hp_tiled, int bits, uint32_t* sigq, const uint16_t* keys_tiled,
                              const uint32_t* sig_keys, int64_t n_rows, int radius, int max_cand, uint32_t* cnt,

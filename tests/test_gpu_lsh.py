@@ -198,6 +198,43 @@ def test_lsh_edges(lc):
     c.close()
 
 
+@pytest.mark.parametrize("bits", list(range(32, 257, 32)))
+def test_signatures_at_tile_edges(lc, bits):
+    """Every signature width, on inserts whose rows start and end inside and at the edges of the signature
+    kernels' tiles (16-row groups, 256- and 512-row tiles, a single wave's rows), at both sides of the row count
+    where the bulk kernel takes over.  Away from EPS the bits equal the float64 signs; a query equal to a
+    stored row gets that row's signature (radius 0 finds it)."""
+    import torch
+    for d, parts in ((100, (37, 4096, 1, 4097)), (700, (4097 + 511, 16, 5000)), (200, (4097, 255, 6000)),
+                     (60, (3 * 512 + 4096,))):
+        N = sum(parts)
+        g = torch.Generator().manual_seed(bits * 1000 + d)
+        keys = torch.randn((N, d), generator=g).to(torch.bfloat16).cuda()
+        keys[N // 2] = 0
+        tok = torch.zeros((N, 1), dtype=torch.int32, device="cuda")
+        hp = torch.randn((bits, d), generator=g).to(torch.bfloat16).cuda()
+        c = lc.LaCache(N, d, 1, lc.BF16, 64, 0)
+        c.enable_lsh(bits, hp, 8)
+        r0 = 0
+        for n in parts:
+            c.insert(keys[r0:r0 + n], keys[r0:r0 + n], tok[r0:r0 + n])
+            r0 += n
+        ones = c.export_signatures(0, N).cpu()
+        c.enable_lsh(bits, hp, 8)                     # the whole store at once
+        assert torch.equal(ones, c.export_signatures(0, N).cpu())
+        z = c.export(0, N)[0].view(torch.bfloat16).double()
+        proj = (z @ hp.double().T).cpu().numpy()
+        got = np.unpackbits(ones.numpy().view(np.uint8), axis=-1, bitorder="little").astype(bool)
+        bad = (got != (proj >= 0)) & (np.abs(proj) >= EPS)
+        assert not bad.any(), (d, np.argwhere(bad)[:10])
+        assert got[N // 2].all()                      # a zero vector projects to zero, which counts as >= 0
+        rows = torch.randint(N, (64,), generator=g).cuda()
+        out = c.lookup_lsh(keys[rows], keys[rows], tok[rows], 0.9, 0.85, 1, 0)
+        live = (rows != N // 2).cpu()
+        assert torch.equal(out[0].cpu()[live].long(), rows.cpu()[live])
+        c.close()
+
+
 def test_lsh_recall_full_size_serve(lc):
     """The serving workload at full size (1M x 768, 4096 queries): 256-bit signatures, radius 64.  Against
     the exact lookup every stage-1 hit is found (same entry, same decision) and the candidate lists stay
