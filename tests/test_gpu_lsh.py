@@ -235,6 +235,44 @@ def test_signatures_at_tile_edges(lc, bits):
         c.close()
 
 
+@pytest.mark.parametrize("bits", list(range(32, 257, 32)))
+def test_candidate_scan_at_block_edges(lc, bits):
+    """The candidates of every signature width, at store sizes around the scan's 16- and 64-entry blocks and its
+    turns, and query counts around its 16-query blocks, its largest chunk and the count below which it runs on
+    the vector ALU: counts equal to the Hamming distances of the exported signatures (whole numbers), and the
+    winner the best of exactly those candidates."""
+    import torch
+    d, g = 64, torch.Generator().manual_seed(bits)
+    hp = torch.randn((bits, d), generator=g).to(torch.bfloat16).cuda()
+    for N, B in ((1, 4), (15, 1), (63, 3), (64, 16), (65, 17), (1025, 100), (5000, 480), (4099, 481), (300001, 30)):
+        keys = torch.randn((N, d), generator=g).to(torch.bfloat16).cuda()
+        q = torch.randn((B, d), generator=g).to(torch.bfloat16).cuda()
+        q[0], q[B // 2], q[B - 1] = keys[0], keys[N // 2], keys[N - 1]
+        tok = torch.zeros((max(N, B), 1), dtype=torch.int32, device="cuda")
+        c, cq = (lc.LaCache(n, d, 1, lc.BF16, 512, 0) for n in (N, B))
+        for x, rows in ((c, keys), (cq, q)):
+            x.insert(rows, rows, tok[:rows.shape[0]])
+            x.enable_lsh(bits, hp, 4096)
+        sig = c.export_signatures(0, N).view(torch.uint8)
+        sq = cq.export_signatures(0, B).view(torch.uint8)
+        unpack = lambda x: ((x[..., None] >> torch.arange(8, device="cuda", dtype=torch.uint8)) & 1).flatten(1)  # noqa: E731
+        kb, qb = unpack(sig).float(), unpack(sq).float()
+        dist = (qb.sum(1)[:, None] + kb.sum(1)[None] - 2 * qb @ kb.T).round().int()
+        z, zq = (x.export(0, n)[0].view(torch.bfloat16).float() for x, n in ((c, N), (cq, B)))
+        scores = zq @ z.T
+        for radius in (0, bits // 4, bits // 2 - 3 * (N > 5000)):
+            idx, score, _, _, n_cand = c.lookup_lsh(q, q, tok[:B], -1.0, 2.0, 1, radius)
+            cand = dist <= radius
+            assert torch.equal(n_cand.long(), cand.sum(1)), (N, B, radius)
+            kept = (cand.sum(1) > 0) & (cand.sum(1) <= 4096)
+            best = torch.where(cand, scores, -2.0).max(1).values.clamp(-1, 1)   # reported scores are clamped
+            assert torch.all(idx[~(cand.sum(1) > 0)] == -1)
+            assert torch.all((score - best)[kept].abs() <= 1e-5), (N, B, radius)
+            assert torch.all(cand[torch.arange(B, device="cuda")[kept], idx[kept].long()])
+        c.close()
+        cq.close()
+
+
 def test_lsh_recall_full_size_serve(lc):
     """The serving workload at full size (1M x 768, 4096 queries): 256-bit signatures, radius 64.  Against
     the exact lookup every stage-1 hit is found (same entry, same decision) and the candidate lists stay
