@@ -146,23 +146,72 @@ __device__ inline void load8(const void* row, int dtype, int d, int j0, double v
 
 // ---------------------------------------------------------------------------
 // Wave-wide butterfly reductions: every lane ends with the same value, and
-// the combination order is fixed, so results are run-to-run identical.
+// the combination order is fixed (lanes 32 apart first, then 16, 8, 4, 2, 1),
+// so results are run-to-run identical.  The exchanges run on the vector ALU
+// (DPP and the row swaps), not through LDS: a step costs a few cycles
+// instead of an LDS round trip, and these chains are most of what the
+// kernels of a small call wait for.
 // ---------------------------------------------------------------------------
+// {a, b} = {x of this lane, x of lane ^ M}, in an order that every half of a wider value shares.
+template <int M>
+__device__ __forceinline__ void xor_exchange(uint32_t x, uint32_t& a, uint32_t& b) {
+    if constexpr (M == 32 || M == 16) {
+        const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(x, x, false, false)
+                               : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        a = r[0], b = r[1];
+    } else {
+        a = x;
+        if constexpr (M == 8) b = __builtin_amdgcn_update_dpp(x, x, 0x128, 0xF, 0xF, false);  // row_ror:8
+        if constexpr (M == 4) {  // even groups of 4 lanes take from 4 above, odd ones from 4 below
+            b = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xF, 0x5, false);
+            b = __builtin_amdgcn_update_dpp(b, x, 0x114, 0xF, 0xA, false);
+        }
+        if constexpr (M == 2) b = __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false);  // quad_perm 2,3,0,1
+        if constexpr (M == 1) b = __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false);  // quad_perm 1,0,3,2
+    }
+}
+template <int M, class T, class Op>
+__device__ __forceinline__ T xor_combine(T x, Op op) {
+    if constexpr (sizeof(T) == 4) {
+        uint32_t a, b;
+        xor_exchange<M>(__builtin_bit_cast(uint32_t, x), a, b);
+        return op(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b));
+    } else {
+        const uint64_t u = __builtin_bit_cast(uint64_t, x);
+        uint32_t al, bl, ah, bh;
+        xor_exchange<M>((uint32_t)u, al, bl);
+        xor_exchange<M>((uint32_t)(u >> 32), ah, bh);
+        return op(__builtin_bit_cast(T, (uint64_t)ah << 32 | al), __builtin_bit_cast(T, (uint64_t)bh << 32 | bl));
+    }
+}
+template <class T, class Op>
+__device__ __forceinline__ T wave_reduce(T x, Op op) {
+    x = xor_combine<32>(x, op);
+    x = xor_combine<16>(x, op);
+    x = xor_combine<8>(x, op);
+    x = xor_combine<4>(x, op);
+    x = xor_combine<2>(x, op);
+    return xor_combine<1>(x, op);
+}
 __device__ inline double wave_sum_f64(double x) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, kWave);
-    return x;
+    return wave_reduce(x, [](double a, double b) { return a + b; });
 }
 __device__ inline float wave_sum_f32(float x) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, kWave);
-    return x;
+    return wave_reduce(x, [](float a, float b) { return a + b; });
 }
 __device__ inline uint64_t umax64(uint64_t a, uint64_t b) { return a > b ? a : b; }
-__device__ inline uint64_t wave_max_u64(uint64_t x) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x = umax64(x, (uint64_t)__shfl_xor((unsigned long long)x, m, kWave));
-    return x;
+__device__ inline uint64_t wave_max_u64(uint64_t x) { return wave_reduce(x, umax64); }
+
+// ---------------------------------------------------------------------------
+// "The last workgroup to finish goes on": every workgroup publishes its part with device-wide atomic
+// operations only, calls this, and after a workgroup barrier one thread adds 1 to a counter; the workgroup
+// that counts last reads the parts with device-wide atomic loads.  Atomic operations take effect where all
+// XCDs see them, and the wait returns when this wave's have: they are ordered before the counter without
+// writing the XCD's L2 back, as a device-wide release fence does (25 us per pass of 256 workgroups).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void last_workgroup_wait() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
 }
 
 // ---------------------------------------------------------------------------

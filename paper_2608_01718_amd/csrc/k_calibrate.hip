@@ -10,8 +10,8 @@
 // say; this is numpy's default), from the two order statistics floor(h) and
 // floor(h) + 1, which an exact radix select finds without sorting: three
 // histogram passes over the orderable 32-bit keys of the similarities (11,
-// 11 and 10 bits), each followed by a one-workgroup scan that fixes those
-// bits of both ranks' keys.
+// 11 and 10 bits), each ended by a scan, in the workgroup that finishes last,
+// that fixes those bits of both ranks' keys (1M similarities: 12 + 9 + 9 us).
 #include <mutex>
 
 #include "common.hpp"
@@ -28,14 +28,111 @@ __constant__ const int kBits[kPasses] = {11, 11, 10};
 
 }  // namespace
 
-// One wave per pair (grid-stride over the pairs): normalise a[j] and b[j] as stored vectors are, and dot the
-// rounded values in column order per lane, then across the wave.  The rounded values are used as float32
-// directly (a bfloat16 is a float32 with zero low bits); products of two are exact.  NC > 0: d <= 512 NC and each lane keeps its 8 NC columns of
-// both rows in registers, read once; the norms are summed in the order row_norm uses, so the rounded values
-// are those of the stored vectors.  NC = 0: any d, the rows read once for the norms and once for the dot.
+// The elements of a row in registers: lane l keeps columns 8 l + 512 c .. + 7 for c < NC, zeros beyond d.  Rows of
+// whole 16-byte chunks (fast) are loaded without branches, every load issued before the first is used, and
+// non-temporally (each row is read once); others element by element.
+template <int NC>
+__device__ __forceinline__ void load_pair(const char* ra, const char* rb, int dtype, int d, bool fast, int lane,
+                                          float (&xa)[NC][8], float (&xb)[NC][8]) {
+    if (!fast) {
+        row_to_regs<NC>(ra, dtype, d, true, lane, xa);
+        row_to_regs<NC>(rb, dtype, d, true, lane, xb);
+        return;
+    }
+    auto at = [&](const char* r, int c, int half) {  // lanes past the row read its first chunk, and drop it
+        const int j0 = lane * 8 + 512 * c;
+        const size_t off = j0 < d ? (size_t)j0 * (dtype == 0 ? 4 : 2) + 16 * half : 0;
+        return __builtin_nontemporal_load((const u32x4*)(r + off));
+    };
+    if (dtype == 0) {
+        u32x4 a[NC][2], b[NC][2];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) a[c][h] = at(ra, c, h), b[c][h] = at(rb, c, h);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const bool in = lane * 8 + 512 * c < d;
+                xa[c][e] = in ? __uint_as_float(a[c][e >> 2][e & 3]) : 0.0f;
+                xb[c][e] = in ? __uint_as_float(b[c][e >> 2][e & 3]) : 0.0f;
+            }
+    } else {
+        u32x4 a[NC], b[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) a[c] = at(ra, c, 0), b[c] = at(rb, c, 0);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const bool in = lane * 8 + 512 * c < d;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t u = in ? a[c][t] : 0u, v = in ? b[c][t] : 0u;
+                xa[c][2 * t] = __uint_as_float(u << 16), xa[c][2 * t + 1] = __uint_as_float(u & 0xFFFF0000u);
+                xb[c][2 * t] = __uint_as_float(v << 16), xb[c][2 * t + 1] = __uint_as_float(v & 0xFFFF0000u);
+            }
+        }
+    }
+}
+
+// The row divided by its norm and rounded to bfloat16, two values to a word, as bf16_rne_quotient rounds each:
+// the float32 products are rounded in pairs, and a lane with a product that the proof of bf16_rne_quotient_fast
+// does not cover (within 2 units of a rounding midpoint, or below 2^-125) goes through the division for it.
+// One element in 13,000 is such a one, 7 % of 1024-column rows hold any, so the test is made once per row and
+// the loop over a lane's elements is left out of the common path.  rnf = quotient_rcp_f32(n).
+template <int NC>
+__device__ __forceinline__ void quantise_row(const float (&x)[NC][8], double n, float rnf, int d, int lane,
+                                             uint32_t (&p)[NC * 4]) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    constexpr uint32_t kTiny = 0x01000000u;  // bits of 2^-125
+    uint16_t window = 0xFFFFu;
+    float least = __builtin_inff();
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        float low = __builtin_inff();
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float f0 = x[c][2 * t] * rnf, f1 = x[c][2 * t + 1] * rnf;
+            const uint16_t w0 = (uint16_t)(__float_as_uint(f0) - 0x7FFEu);
+            const uint16_t w1 = (uint16_t)(__float_as_uint(f1) - 0x7FFEu);
+            window = w0 < window ? w0 : window;
+            window = w1 < window ? w1 : window;
+            low = fminf(fminf(__builtin_fabsf(f0), __builtin_fabsf(f1)), low);
+            p[c * 4 + t] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{f0, f1}), bf16x2));
+        }
+        if (lane * 8 + 512 * c < d) least = fminf(least, low);
+    }
+    if (__ballot(window <= 4u || least < __uint_as_float(kTiny)) == 0ull) return;
+    uint32_t todo = 0u;  // the lane's elements that need the division (zeros are exact as they are)
+#pragma unroll
+    for (int i = 0; i < NC * 8; ++i) {
+        const float v = x[i >> 3][i & 7];
+        const uint32_t u = __float_as_uint(v * rnf);
+        if ((u & 0xFFFFu) - 0x7FFEu <= 4u || ((u & 0x7FFFFFFFu) < kTiny && v != 0.0f)) todo |= 1u << i;
+    }
+    while (__ballot(todo != 0u) != 0ull) {
+        const int i = todo != 0u ? __ffs(todo) - 1 : NC * 8;
+        float v = 0.0f;
+#pragma unroll
+        for (int k = 0; k < NC * 8; ++k) v = k == i ? x[k >> 3][k & 7] : v;
+        const uint32_t h = bf16_rne_from_f64((double)v / n);
+#pragma unroll
+        for (int k = 0; k < NC * 4; ++k)
+            if (k == i >> 1) p[k] = (i & 1) ? (p[k] & 0xFFFFu) | (h << 16) : (p[k] & 0xFFFF0000u) | h;
+        todo &= todo - 1u;
+    }
+}
+
+// One wave per pair: normalise a[j] and b[j] as stored vectors are, and dot the rounded values in column order per
+// lane, then across the wave (products of two bfloat16 values are exact in float32).  NC > 0: d <= 512 NC and each
+// lane keeps its 8 NC columns of both rows in registers, read once; the norms are summed in the order row_norm
+// uses, so the rounded values are those of the stored vectors.  Square root and reciprocal, 60 double-precision
+// operations that every lane needs of both norms, run once for the two (one norm in each half of the wave).
+// NC = 0: any d, the rows read once for the norms and once for the dot.
 template <int NC>
 __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const void* __restrict__ b, int dtype, int d,
-                                   int64_t j, float* __restrict__ sims) {
+                                            bool fast, int64_t j, float* __restrict__ sims) {
     const int lane = threadIdx.x & 63;
     const size_t esz = dtype == 0 ? 4 : 2;
     const char* ra = (const char*)a + j * d * esz;
@@ -43,11 +140,7 @@ __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const vo
     float acc = 0.0f;
     if constexpr (NC > 0) {
         float xa[NC][8], xb[NC][8];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            load8f(ra, dtype, d, lane * 8 + 512 * c, xa[c]);
-            load8f(rb, dtype, d, lane * 8 + 512 * c, xb[c]);
-        }
+        load_pair<NC>(ra, rb, dtype, d, fast, lane, xa, xb);
         double sa = 0.0, sb = 0.0;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -56,16 +149,21 @@ __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const vo
                 sa += (double)xa[c][e] * (double)xa[c][e];
                 sb += (double)xb[c][e] * (double)xb[c][e];
             }
-        const double na = __builtin_sqrt(wave_sum_f64(sa)), nb = __builtin_sqrt(wave_sum_f64(sb));
-        if (na != 0.0 && nb != 0.0) {  // a zero vector normalises to zero and scores 0
-            const float rna = quotient_rcp_f32(na), rnb = quotient_rcp_f32(nb);
+        sa = wave_sum_f64(sa), sb = wave_sum_f64(sb);
+        const double n = __builtin_sqrt(lane < 32 ? sa : sb);
+        const float rnf = quotient_rcp_f32(n);
+        const double na = __shfl(n, 0, kWave), nb = __shfl(n, 32, kWave);
+        const float rna = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rnf), 0));
+        const float rnb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rnf), 32));
+        if (__ballot(n == 0.0) == 0ull) {  // a zero vector normalises to zero and scores 0
+            uint32_t pa[NC * 4], pb[NC * 4];
+            quantise_row<NC>(xa, na, rna, d, lane, pa);
+            quantise_row<NC>(xb, nb, rnb, d, lane, pb);
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    if (lane * 8 + 512 * c + e >= d) continue;
-                    acc += bf16_rne_quotient_f32(xa[c][e], na, rna) * bf16_rne_quotient_f32(xb[c][e], nb, rnb);
-                }
+            for (int k = 0; k < NC * 4; ++k) {
+                acc += __uint_as_float(pa[k] << 16) * __uint_as_float(pb[k] << 16);
+                acc += __uint_as_float(pa[k] & 0xFFFF0000u) * __uint_as_float(pb[k] & 0xFFFF0000u);
+            }
         }
     } else {
         const double na = row_norm(ra, dtype, d, true, lane);
@@ -88,74 +186,86 @@ __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const vo
     if (lane == 0) sims[j] = fminf(fmaxf(acc, -1.0f), 1.0f);
 }
 
+// state[0..1]: the key bits found so far for rank 0 / rank 1; state[2..3]: the ranks still to skip inside the
+// current prefix; state[4]: workgroups that have added their histogram.  hist: [2][kBins] counts.
+__device__ inline void select_init(uint32_t* state, uint32_t* hist, uint32_t r0, uint32_t r1) {
+    for (int i = threadIdx.x; i < 2 * kBins; i += blockDim.x) hist[i] = 0u;
+    if (threadIdx.x < 5) state[threadIdx.x] = threadIdx.x == 2 ? r0 : threadIdx.x == 3 ? r1 : 0u;
+}
+
+// The pair cosines; the first workgroup also sets up the selection that follows on the stream.
 // LOOP: grid-stride over the pairs, for more pairs than one grid holds; else one pair per wave (the loop's
-// carried state costs registers, and with them occupancy, on this latency-bound kernel).
+// carried state costs registers, and with them occupancy).
+// Bound by the vector ALU beside HBM.  1M pairs of 1024 bfloat16 columns: 710 us (5.8 TB/s), 945 us with the rounding
+// test and its division branch at every element, both norms in every lane and loads that waited for each other.
 template <int NC, bool LOOP>
 __global__ __launch_bounds__(256) void k_pair_cosine(const void* __restrict__ a, const void* __restrict__ b,
-                                                     int dtype, int d, int64_t n, float* __restrict__ sims) {
-    const int64_t j0 = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                     int dtype, int d, int64_t n, float* __restrict__ sims,
+                                                     uint32_t* __restrict__ state, uint32_t* __restrict__ hist,
+                                                     uint32_t r0, uint32_t r1) {
+    if (blockIdx.x == 0) select_init(state, hist, r0, r1);
+    const bool fast = (((uintptr_t)a | (uintptr_t)b) & 15) == 0 && d % 8 == 0;  // every row 16-byte aligned
+    const int64_t j0 = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (LOOP) {
-        for (int64_t j = j0; j < n; j += (int64_t)gridDim.x * 4) pair_cosine<NC>(a, b, dtype, d, j, sims);
+        for (int64_t j = j0; j < n; j += (int64_t)gridDim.x * 4) pair_cosine<NC>(a, b, dtype, d, fast, j, sims);
     } else {
         if (j0 >= n) return;
-        pair_cosine<NC>(a, b, dtype, d, j0, sims);
+        pair_cosine<NC>(a, b, dtype, d, fast, j0, sims);
     }
 }
 
-// state[0..1]: the key bits found so far for rank 0 / rank 1; state[2..3]: the ranks still to skip inside
-// the current prefix.  hist: [2][kBins] counts.
-__global__ __launch_bounds__(256) void k_select_init(uint32_t* __restrict__ state, uint32_t* __restrict__ hist,
-                                                     uint32_t r0, uint32_t r1) {
-    for (int i = threadIdx.x; i < 2 * kBins; i += blockDim.x) hist[i] = 0u;
-    if (threadIdx.x == 0) {
-        state[0] = 0u;
-        state[1] = 0u;
-        state[2] = r0;
-        state[3] = r1;
+// Adds 1 to h[bin] for the lanes with `on`.  Similarities crowd into few bins (cosines of 0.5 .. 1 share all but the
+// last two bits of the first pass), so the lanes that agree with the first one are counted by one addition.
+__device__ inline void hist_add(uint32_t* h, uint32_t bin, bool on) {
+    const uint64_t m = __ballot(on);
+    if (m == 0ull) return;
+    const uint32_t lead = (uint32_t)__builtin_amdgcn_readlane((int)bin, __ffsll((unsigned long long)m) - 1);
+    const uint64_t same = __ballot(on && bin == lead);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&h[lead], (uint32_t)__popcll(same));
+    if (on && bin != lead) atomicAdd(&h[bin], 1u);
+}
+
+// Histogram (in LDS) of bits [shift, shift + bits) of the keys whose higher bits equal each rank's prefix p0, p1;
+// only the first one while the prefixes are equal.  Elements first, first + step, ... of sims.
+__device__ inline void select_count(const float* __restrict__ sims, int64_t n, int64_t first, int64_t step, int pass,
+                                    uint32_t p0, uint32_t p1, uint32_t* h) {
+    const int shift = kShift[pass], hi = shift + kBits[pass];  // bits above hi are fixed by the earlier passes
+    const uint32_t mask = (uint32_t)((1u << kBits[pass]) - 1u);
+    const bool two = p0 != p1;
+    constexpr int kAhead = 8;  // similarities on their way at once
+    for (int64_t i0 = first; i0 - (int)(threadIdx.x & 63) < n; i0 += kAhead * step) {  // whole waves
+        float v[kAhead];
+#pragma unroll
+        for (int t = 0; t < kAhead; ++t) v[t] = i0 + t * step < n ? sims[i0 + t * step] : 0.0f;
+#pragma unroll
+        for (int t = 0; t < kAhead; ++t) {
+            const bool in = i0 + t * step < n;
+            const uint32_t key = order_f32(v[t]);
+            const uint32_t bin = (key >> shift) & mask;
+            hist_add(h, bin, in && (hi >= 32 || (key >> hi) == (p0 >> hi)));
+            if (two) hist_add(h + kBins, bin, in && (key >> hi) == (p1 >> hi));
+        }
     }
 }
 
-// Histogram of bits [shift, shift + bits) of the keys whose higher bits equal each rank's prefix.
-__global__ __launch_bounds__(256) void k_select_hist(const float* __restrict__ sims, int64_t n, int pass,
-                                                     const uint32_t* __restrict__ state,
-                                                     uint32_t* __restrict__ hist) {
-    __shared__ uint32_t h[2 * kBins];
-    for (int i = threadIdx.x; i < 2 * kBins; i += blockDim.x) h[i] = 0u;
-    __syncthreads();
-    const int shift = kShift[pass], bits = kBits[pass];
-    const int hi = shift + bits;  // bits above hi are fixed by the earlier passes
-    const uint32_t p0 = state[0], p1 = state[1];
-    const uint32_t mask = (uint32_t)((1u << bits) - 1u);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t key = order_f32(sims[i]);
-        const uint32_t bin = (key >> shift) & mask;
-        const bool m0 = hi >= 32 || (key >> hi) == (p0 >> hi);
-        const bool m1 = hi >= 32 || (key >> hi) == (p1 >> hi);
-        if (m0) atomicAdd(&h[bin], 1u);
-        if (m1) atomicAdd(&h[kBins + bin], 1u);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < 2 * kBins; i += blockDim.x)
-        if (h[i] != 0u) atomicAdd(&hist[i], h[i]);
-}
+constexpr int kSelectThreads = 1024;
 
-// One workgroup: for each rank, the bin holding it (counts scanned in bin order) fixes this pass's bits of its
-// key; the counts of the bins before it are skipped.  Each thread takes nb / 256 consecutive bins, a block-wide
-// exclusive scan gives the count before them, and the one thread whose bins hold the rank walks them.  The
-// histogram is cleared for the next pass.
-__global__ __launch_bounds__(256) void k_select_scan(int pass, uint32_t* __restrict__ state,
-                                                     uint32_t* __restrict__ hist) {
-    constexpr int kPer = kBins / 256;  // bins per thread in the widest pass
-    __shared__ uint32_t wsum[2][4];
+// One workgroup of T threads: for each rank, the bin holding it (counts read through count(i), scanned in bin
+// order) fixes this pass's bits of its key; the counts of the bins before it are skipped.  Each thread takes
+// kBins / T consecutive bins, a block-wide exclusive scan gives the count before them, and the one thread whose
+// bins hold the rank walks them.  `state` may be LDS or global memory.
+template <int T, class Count>
+__device__ inline void select_scan(int pass, uint32_t* state, bool two, Count count, uint32_t (&wsum)[2][T / 64]) {
+    constexpr int kPer = kBins / T;  // bins per thread in the widest pass
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int shift = kShift[pass], per = (1 << kBits[pass]) / 256;
+    const int shift = kShift[pass], per = (1 << kBits[pass]) / T;
     const uint32_t rank[2] = {state[2], state[3]};
     uint32_t cnt[2][kPer], tot[2] = {0u, 0u};
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            cnt[k][i] = i < per ? hist[k * kBins + tid * per + i] : 0u;
+            cnt[k][i] = i < per ? count((two ? k * kBins : 0) + tid * per + i) : 0u;
             tot[k] += cnt[k][i];
         }
     uint32_t incl[2];
@@ -189,14 +299,11 @@ __global__ __launch_bounds__(256) void k_select_scan(int pass, uint32_t* __restr
             }
         }
     }
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-        for (int i = 0; i < per; ++i) hist[k * kBins + tid * per + i] = 0u;
+    __syncthreads();
 }
 
 // P = x_lo + (h - lo) (x_hi - x_lo) in double from the two order statistics; out[0] = P, out[1] = min(cap, P).
-__global__ void k_select_final(const uint32_t* __restrict__ state, double frac, float cap, float* __restrict__ out) {
-    if (threadIdx.x != 0) return;
+__device__ inline void select_result(const uint32_t* state, double frac, float cap, float* __restrict__ out) {
     const double lo = (double)unorder_f32(state[0]);
     const double hi = (double)unorder_f32(state[1]);
     const double P = lo + frac * (hi - lo);
@@ -204,9 +311,63 @@ __global__ void k_select_final(const uint32_t* __restrict__ state, double frac, 
     out[1] = (float)fmin((double)cap, P);
 }
 
+// One pass of the selection over many similarities: every workgroup adds its histogram to the global one, and the
+// last one to do so (no workgroup waits for another) scans it, clears it for the next pass and, in the last pass,
+// writes the result.
+__global__ __launch_bounds__(kSelectThreads) void k_select_pass(const float* __restrict__ sims, int64_t n, int pass,
+                                                     uint32_t* __restrict__ state, uint32_t* __restrict__ hist,
+                                                     double frac, float cap, float* __restrict__ out) {
+    __shared__ uint32_t h[2 * kBins];
+    __shared__ uint32_t wsum[2][kSelectThreads / 64];
+    __shared__ bool last;
+    const int tid = threadIdx.x;
+    const uint32_t p0 = state[0], p1 = state[1];
+    const bool two = p0 != p1;
+    const int bins = two ? 2 * kBins : kBins;
+    for (int i = tid; i < bins; i += kSelectThreads) h[i] = 0u;
+    __syncthreads();
+    select_count(sims, n, (int64_t)blockIdx.x * kSelectThreads + tid,
+                 (int64_t)gridDim.x * kSelectThreads, pass, p0, p1, h);
+    __syncthreads();
+    for (int i = tid; i < bins; i += kSelectThreads)
+        if (h[i] != 0u) atomicAdd(&hist[i], h[i]);
+    last_workgroup_wait();
+    __syncthreads();
+    if (tid == 0) last = atomicAdd(&state[4], 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    select_scan<kSelectThreads>(pass, state, two, [&](int i) {
+        return __hip_atomic_load(&hist[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }, wsum);
+    for (int i = tid; i < bins; i += kSelectThreads) hist[i] = 0u;
+    if (tid == 0) {
+        state[4] = 0u;
+        if (pass == kPasses - 1) select_result(state, frac, cap, out);
+    }
+}
+
+// The whole selection over few similarities in one workgroup.
+__global__ __launch_bounds__(kSelectThreads) void k_select_few(const float* __restrict__ sims, int64_t n, uint32_t r0,
+                                                     uint32_t r1, double frac, float cap, float* __restrict__ out) {
+    __shared__ uint32_t h[2 * kBins];
+    __shared__ uint32_t state[5];
+    __shared__ uint32_t wsum[2][kSelectThreads / 64];
+    select_init(state, h, r0, r1);
+    __syncthreads();
+    for (int pass = 0; pass < kPasses; ++pass) {
+        const uint32_t p0 = state[0], p1 = state[1];
+        select_count(sims, n, threadIdx.x, kSelectThreads, pass, p0, p1, h);
+        __syncthreads();
+        select_scan<kSelectThreads>(pass, state, p0 != p1, [&](int i) { return h[i]; }, wsum);
+        for (int i = threadIdx.x; i < 2 * kBins; i += kSelectThreads) h[i] = 0u;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) select_result(state, frac, cap, out);
+}
+
 // Scratch of the allocation-free calibration entry point (lacache_calibrate_noalloc): the selection's state
 // and histograms, kCalibScratchWords words.  Every GPU the library runs on holds its own copy for the life of
-// the process; all such calls on one GPU share it (k_select_init clears it at the start of each call, so calls
+// the process; all such calls on one GPU share it (the pair kernel clears it at the start of each call, so calls
 // ordered on one stream are independent; calls that overlap on one GPU race).
 static __device__ __align__(256) uint32_t scratch[kCalibScratchWords];
 
@@ -231,6 +392,10 @@ hipError_t calibrate_static_scratch(uint32_t** out) {
     return hipSuccess;
 }
 
+// Similarities up to which one workgroup selects, in one launch instead of three.  Whole call, one workgroup / many,
+// us: 14 / 22 for 500 pairs, 18 / 26 for 4096, 34 / 41 for 16384, 56 / 48 for 32768 (nine launches: 31, 45, 52, 64).
+constexpr int64_t kSelectFew = 16384;
+
 hipError_t launch_calibrate(const void* a, const void* b, int dtype, int d, int64_t n, float percentile, float cap,
                             float* sims, float* tau, uint32_t* scratch, int num_cu, hipStream_t s) {
     if (n <= 0) return hipErrorInvalidValue;
@@ -241,35 +406,32 @@ hipError_t launch_calibrate(const void* a, const void* b, int dtype, int d, int6
     const double frac = lo == hi ? 0.0 : h - (double)lo;
     uint32_t* state = scratch;
     uint32_t* hist = scratch + 64;
-    const dim3 pc_grid((unsigned)grid_blocks((n + 3) / 4)), pc_block(256);
-    if ((n + 3) / 4 > kMaxGridBlocks) {
-        if (d <= 512)
-            k_pair_cosine<1, true><<<pc_grid, pc_block, 0, s>>>(a, b, dtype, d, n, sims);
-        else if (d <= 1024)
-            k_pair_cosine<2, true><<<pc_grid, pc_block, 0, s>>>(a, b, dtype, d, n, sims);
-        else if (d <= 2048)
-            k_pair_cosine<4, true><<<pc_grid, pc_block, 0, s>>>(a, b, dtype, d, n, sims);
-        else
-            k_pair_cosine<0, true><<<pc_grid, pc_block, 0, s>>>(a, b, dtype, d, n, sims);
-    } else {
-        if (d <= 512)
-            k_pair_cosine<1, false><<<pc_grid, pc_block, 0, s>>>(a, b, dtype, d, n, sims);
-        else if (d <= 1024)
-            k_pair_cosine<2, false><<<pc_grid, pc_block, 0, s>>>(a, b, dtype, d, n, sims);
-        else if (d <= 2048)
-            k_pair_cosine<4, false><<<pc_grid, pc_block, 0, s>>>(a, b, dtype, d, n, sims);
-        else
-            k_pair_cosine<0, false><<<pc_grid, pc_block, 0, s>>>(a, b, dtype, d, n, sims);
+    const dim3 grid((unsigned)grid_blocks((n + 3) / 4)), block(256);
+    const bool loop = (n + 3) / 4 > kMaxGridBlocks;
+    auto pairs = [&](auto looped, auto single) {
+        (loop ? looped : single)<<<grid, block, 0, s>>>(a, b, dtype, d, n, sims, state, hist, (uint32_t)lo,
+                                                        (uint32_t)hi);
+    };
+    if (d <= 512)
+        pairs(k_pair_cosine<1, true>, k_pair_cosine<1, false>);
+    else if (d <= 1024)
+        pairs(k_pair_cosine<2, true>, k_pair_cosine<2, false>);
+    else if (d <= 2048)
+        pairs(k_pair_cosine<4, true>, k_pair_cosine<4, false>);
+    else
+        pairs(k_pair_cosine<0, true>, k_pair_cosine<0, false>);
+    if (n <= kSelectFew) {
+        k_select_few<<<dim3(1), dim3(kSelectThreads), 0, s>>>(sims, n, (uint32_t)lo, (uint32_t)hi, frac, cap, tau);
+        return hipGetLastError();
     }
-    k_select_init<<<dim3(1), dim3(256), 0, s>>>(state, hist, (uint32_t)lo, (uint32_t)hi);
-    // at least 16 similarities per thread: each workgroup adds its non-zero bins to the global histogram
-    int64_t blocks = (n + 256 * 16 - 1) / (256 * 16);
-    if (blocks > num_cu) blocks = num_cu;
-    for (int pass = 0; pass < kPasses; ++pass) {
-        k_select_hist<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(sims, n, pass, state, hist);
-        k_select_scan<<<dim3(1), dim3(256), 0, s>>>(pass, state, hist);
-    }
-    k_select_final<<<dim3(1), dim3(64), 0, s>>>(state, frac, cap, tau);
+    // at least 16 similarities per thread, and few workgroups: each adds its non-zero bins to the global histogram
+    // and counts itself, at the same few addresses as the others
+    int64_t blocks = (n + kSelectThreads * 16 - 1) / (kSelectThreads * 16);
+    if (blocks > num_cu / 2) blocks = num_cu / 2;
+    if (blocks < 1) blocks = 1;
+    for (int pass = 0; pass < kPasses; ++pass)
+        k_select_pass<<<dim3((unsigned)blocks), dim3(kSelectThreads), 0, s>>>(sims, n, pass, state, hist, frac, cap,
+                                                                             tau);
     return hipGetLastError();
 }
 

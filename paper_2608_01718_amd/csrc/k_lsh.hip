@@ -627,8 +627,8 @@ hipError_t launch_simhash(const uint16_t* rows_tiled, int d_pad, int64_t row0, i
 }
 
 template <int W>
-static void launch_scan(const uint32_t* sig_keys, int64_t n_rows, const uint32_t* sigq, int nb, int radius, int max_cand,
-                        uint32_t* cnt, int32_t* cand, int num_cu, hipStream_t s) {
+static void launch_scan(const uint32_t* sig_keys, int64_t n_rows, const uint32_t* sigq, int nb, int radius,
+                        int max_cand, uint32_t* cnt, int32_t* cand, int num_cu, hipStream_t s) {
     const int chunks = (nb + kScanQueries - 1) / kScanQueries;
     const int nblk = ((nb < kScanQueries ? nb : kScanQueries) + 15) / 16;
     const size_t lds = (size_t)nblk * (ScanWords<W>::NM * 1024 + 64);

@@ -254,7 +254,8 @@ int lacache_insert_ensemble(lacache_t h, const void* keys, const void* const* re
     if (hipMemcpyAsync(h->tokens + first * h->k_cap, resp_tokens, (size_t)n * h->k_cap * 4,
                        hipMemcpyDeviceToDevice, s) != hipSuccess)
         return LACACHE_EHIP;
-    if (h->lsh_bits && launch_simhash(h->keys, h->d_pad, first, n, h->hp, h->lsh_bits, h->sig, h->num_cu, s) != hipSuccess)
+    if (h->lsh_bits &&
+        launch_simhash(h->keys, h->d_pad, first, n, h->hp, h->lsh_bits, h->sig, h->num_cu, s) != hipSuccess)
         return LACACHE_EHIP;
     h->size += n;
     if (first_idx) *first_idx = first;

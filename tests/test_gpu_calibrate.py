@@ -189,3 +189,35 @@ def test_calibration_paper_shaped_full_size(lc):
     assert tau[1] == np.float32(0.80) or tau[1] == tau[0]
     say(f"[ok] P5 = {tau[0]:.6f} (oracle {o['P']:.6f}), tau = {tau[1]:.4f}, max |sim diff| {ds.max():.2e}")
     c.close()
+
+
+@pytest.mark.parametrize("in_dtype", [synth.F32, synth.BF16])
+def test_calibration_selection_and_rounding_edges(lc, in_dtype):
+    """Pair counts around the selection's one-workgroup limit and its many-workgroup form, similarities crowded
+    into one bin and spread over both signs, rows that start off a 16-byte boundary, and rows whose quotients
+    need the division: on rounding midpoints, zeros, subnormal quotients, norms without a float32 reciprocal."""
+    import torch
+    rng = np.random.default_rng(5 + in_dtype)
+    for n, spread in ((16383, (0.2, 0.21)), (16384, (0.01, 30.0)), (16385, (0.2, 0.2001)), (70001, (0.05, 5.0))):
+        a, b = _pairs(rng, n, 40, in_dtype, spread=spread, dup_frac=0.3)
+        for p in (0.0, 5.0, 37.3, 100.0):
+            c = lc.LaCache(1, 40, 1, in_dtype, 1, 0)
+            _check(lc, c, a, b, p, 2.0)
+            c.close()
+    for d in (1016, 1024, 1600):
+        n = 400
+        x = rng.standard_normal((n, d)).astype(np.float32)
+        x[:100] = np.exp2(rng.integers(-8, 9, (100, d))).astype(np.float32) * (1 + rng.integers(0, 256, (100, d)) / 256)
+        x[100:150, : d // 2] = 0
+        x[150:200] *= np.float32(2.0) ** rng.integers(-140, -100, (50, d)).astype(np.float32)
+        x[200:230] *= np.float32(1e36)                # norms whose reciprocal is no normal float32
+        x[230:260] *= np.float32(1e-42)
+        a = x if in_dtype == synth.F32 else synth.to_bf16_bits(x)
+        b = np.ascontiguousarray(a[::-1])
+        want = _lane_order_sims(oracle.quantise(a, in_dtype), oracle.quantise(b, in_dtype))
+        da, db = to_dev(a), to_dev(b)
+        shifted = [torch.empty(n * d + 1, dtype=t.dtype, device=t.device)[1:].view(n, d).copy_(t) for t in (da, db)]
+        for pair in ((da, db), shifted):
+            got = lc.lacache_calibrate_noalloc(*pair, 50.0, 2.0)[0].cpu().numpy()
+            bad = np.nonzero(got != want)[0]
+            assert bad.size == 0, (d, bad[:5], got[bad[:5]], want[bad[:5]])
