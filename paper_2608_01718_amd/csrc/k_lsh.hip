@@ -545,11 +545,7 @@ __global__ __launch_bounds__(256) void k_lsh_verify(const u32x4* __restrict__ ke
                                                     const uint32_t* __restrict__ cnt,
                                                     const int32_t* __restrict__ cand, int max_cand,
                                                     int32_t* __restrict__ n_cand, int n_rows, int dtype,
-                                                    const PrefixModels M, const int32_t* __restrict__ la_tok,
-                                                    int k, const int32_t* __restrict__ tokens, int k_cap,
-                                                    float tau_q, int32_t* __restrict__ idx_out,
-                                                    float* __restrict__ score_out, float* __restrict__ resp_out,
-                                                    int32_t* __restrict__ dec_out) {
+                                                    const VerifyArgs v) {
     const int lane = threadIdx.x & 63;
     const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (b >= B) return;
@@ -569,8 +565,7 @@ __global__ __launch_bounds__(256) void k_lsh_verify(const u32x4* __restrict__ ke
         best = umax64(best, pack_top1(acc, i));
     }
     if (lane == 0) n_cand[b] = (int32_t)c_all;
-    verify_query(b, best, unpack_idx(best), unpack_score(best), n_rows, dtype, M, la_tok, k, tokens, k_cap, tau_q,
-                 idx_out, score_out, resp_out, dec_out, lane);
+    verify_query(b, best, unpack_idx(best), unpack_score(best), n_rows, dtype, v, lane);
 }
 
 hipError_t launch_tile_hyperplanes(const uint16_t* src, int bits, int d, int d_pad, uint16_t* dst, hipStream_t s) {
@@ -649,9 +644,7 @@ static void launch_scan(const uint32_t* sig_keys, int64_t n_rows, const uint32_t
 hipError_t launch_lsh_lookup(const void* queries, int dtype, int nb, int d, int d_pad, uint16_t* qt,
                              const uint16_t* hp_tiled, int bits, uint32_t* sigq, const uint16_t* keys_tiled,
                              const uint32_t* sig_keys, int64_t n_rows, int radius, int max_cand, uint32_t* cnt,
-                             int32_t* cand, int32_t* n_cand, const PrefixModels& models, const int32_t* la_tok,
-                             int k, const int32_t* tokens, int k_cap, float tau_q, int32_t* idx, float* score,
-                             float* resp_score, int32_t* decision, int num_cu, hipStream_t s) {
+                             int32_t* cand, int32_t* n_cand, const VerifyArgs& v, int num_cu, hipStream_t s) {
     if (nb <= 0) return hipSuccess;
     const int words = bits >> 5;
     if (words < 1 || words > 8) return hipErrorInvalidValue;
@@ -685,7 +678,7 @@ hipError_t launch_lsh_lookup(const void* queries, int dtype, int nb, int d, int 
     }
     k_lsh_verify<<<dim3((unsigned)((nb + 3) / 4)), dim3(256), 0, s>>>(
         (const u32x4*)keys_tiled, (const u32x4*)qt, d_pad >> 5, nb, cnt, cand, max_cand, n_cand, (int)n_rows,
-        dtype, models, la_tok, k, tokens, k_cap, tau_q, idx, score, resp_score, decision);
+        dtype, v);
     return hipGetLastError();
 }
 

@@ -46,6 +46,8 @@ struct lacache_s {
     uint64_t* part = nullptr;  // [max_batch][kMaxPartials] packed top-1 candidates
     uint32_t* calib = nullptr; // [kCalibScratchWords] state and histograms of the calibration select
     uint32_t* fallbacks = nullptr;  // [1] queries whose stage-1 group replay missed its score (see k_verify.hip)
+    uint32_t* done = nullptr;  // [kDoneWords] counts of finished workgroups of the streaming kernel, zero between
+                               // calls (the second part of the allocation of `fallbacks`)
     // LSH index (lacache_enable_lsh): hyperplanes, key and query signatures, candidate lists
     int lsh_bits = 0, lsh_max_cand = 0;
     uint16_t* hp = nullptr;        // tiled [lsh_bits][d_pad] raw hyperplanes
@@ -200,7 +202,8 @@ int lacache_create_ensemble(lacache_t* out, int64_t capacity, int32_t d, int32_t
     if (rc == LACACHE_OK) rc = alloc_zero((void**)&h->qt, (size_t)h->mb_pad * h->d_pad * 2);
     if (rc == LACACHE_OK) rc = alloc_zero((void**)&h->part, (size_t)h->max_batch * kMaxPartials * 8);
     if (rc == LACACHE_OK) rc = alloc_zero((void**)&h->calib, (size_t)kCalibScratchWords * 4);
-    if (rc == LACACHE_OK) rc = alloc_zero((void**)&h->fallbacks, 4);
+    if (rc == LACACHE_OK) rc = alloc_zero((void**)&h->fallbacks, (size_t)(32 + kDoneWords) * 4);
+    if (rc == LACACHE_OK) h->done = h->fallbacks + 32;
     if (rc == LACACHE_OK && hipDeviceSynchronize() != hipSuccess) rc = LACACHE_EHIP;
     if (rc != LACACHE_OK) {
         free_all(h);
@@ -268,8 +271,7 @@ int lacache_insert(lacache_t h, const void* keys, const void* resp_emb, const in
     return lacache_insert_ensemble(h, keys, &resp_emb, resp_tokens, n, first_idx, stream);
 }
 
-static int lookup_chunk(lacache_t h, const char* queries, const PrefixModels& models, const int32_t* la_tok, int B,
-                        float tau_q, int k, int32_t* idx, float* score, float* resp, int32_t* dec, hipStream_t s) {
+static int lookup_chunk(lacache_t h, const char* queries, int B, const VerifyArgs& v, hipStream_t s) {
     const int n_rows = (int)h->size;
     int P = 0;
     const bool small = B <= (h->b_small >= 0 ? h->b_small : stream_auto_batch(h->d_pad, n_rows));
@@ -282,6 +284,9 @@ static int lookup_chunk(lacache_t h, const char* queries, const PrefixModels& mo
         // itself, saving the staging launch; with more rows per wave its prologue would cost more than that launch
         // (64 queries on 10k x 384 keys: ~5.7 us of prologue against ~4 us of staging), so they are staged
         const bool fused = small && B <= 32 && stream_fused_ncq(h->d_pad) > 0;
+        // its last workgroup also ends the lookup (one launch per call) while its 16 waves, a query each, have at
+        // most two embedding checks to run one after another
+        const bool whole = fused && (B <= 16 || v.models.m == 1);
         if (!fused && launch_normalise(queries, h->dtype, B, rows_pad, h->d, h->d_pad, h->qt, 0, true, s) != hipSuccess)
             return LACACHE_EHIP;
         hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -294,13 +299,15 @@ static int lookup_chunk(lacache_t h, const char* queries, const PrefixModels& mo
         }
         // with profiling on, the events take the stage-1 kernel's own start and end times (launch_timed)
         hipError_t e = small ? launch_stage1_stream(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s,
-                                                    e0, e1, fused ? queries : nullptr, h->dtype, h->d)
+                                                    e0, e1, fused ? queries : nullptr, h->dtype, h->d,
+                                                    whole ? &v : nullptr, h->done)
                              : launch_stage1_gemm(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s,
                                                   e0, e1);
         if (e != hipSuccess) return LACACHE_EHIP;
+        if (whole) return LACACHE_OK;
     }
-    if (launch_finalize_verify(h->part, P, !small, h->keys, h->qt, B, n_rows, h->dtype, h->d, models, la_tok, k,
-                               h->tokens, h->k_cap, tau_q, idx, score, resp, dec, h->fallbacks, s) != hipSuccess)
+    if (launch_finalize_verify(h->part, P, !small, h->keys, h->qt, B, n_rows, h->dtype, h->d, v, h->fallbacks, s) !=
+        hipSuccess)
         return LACACHE_EHIP;
     return LACACHE_OK;
 }
@@ -321,18 +328,25 @@ int lacache_lookup_ensemble(lacache_t h, const void* queries, const void* const*
     const size_t esz = h->dtype == LACACHE_F32 ? 4 : 2;
     for (int b0 = 0; b0 < B; b0 += h->max_batch) {
         const int nb = (B - b0) < h->max_batch ? (B - b0) : h->max_batch;
-        PrefixModels models{};
-        models.m = h->m;
+        VerifyArgs v{};
+        v.models.m = h->m;
         for (int i = 0; i < h->m; ++i) {
-            models.la[i] = (const char*)lookahead_emb[i] + (size_t)b0 * h->d_resp[i] * esz;
-            models.emb[i] = h->emb[i];
-            models.d[i] = h->d_resp[i];
-            models.d_pad[i] = h->d_pad_resp[i];
-            models.tau[i] = tau_r[i];
+            v.models.la[i] = (const char*)lookahead_emb[i] + (size_t)b0 * h->d_resp[i] * esz;
+            v.models.emb[i] = h->emb[i];
+            v.models.d[i] = h->d_resp[i];
+            v.models.d_pad[i] = h->d_pad_resp[i];
+            v.models.tau[i] = tau_r[i];
         }
-        const int rc = lookup_chunk(h, (const char*)queries + (size_t)b0 * h->d * esz, models,
-                                    lookahead_tokens + (size_t)b0 * k, nb, tau_q, k, idx + b0, score + b0,
-                                    resp_score + (size_t)b0 * h->m, decision + b0, (hipStream_t)stream);
+        v.la_tok = lookahead_tokens + (size_t)b0 * k;
+        v.k = k;
+        v.tokens = h->tokens;
+        v.k_cap = h->k_cap;
+        v.tau_q = tau_q;
+        v.idx = idx + b0;
+        v.score = score + b0;
+        v.resp_score = resp_score + (size_t)b0 * h->m;
+        v.decision = decision + b0;
+        const int rc = lookup_chunk(h, (const char*)queries + (size_t)b0 * h->d * esz, nb, v, (hipStream_t)stream);
         if (rc != LACACHE_OK) return rc;
     }
     return LACACHE_OK;
@@ -468,17 +482,25 @@ int lacache_lookup_lsh(lacache_t h, const void* queries, const void* lookahead_e
     for (int b0 = 0; b0 < B; b0 += h->max_batch) {
         const int nb = (B - b0) < h->max_batch ? (B - b0) : h->max_batch;
         const char* q = (const char*)queries + (size_t)b0 * h->d * esz;
-        PrefixModels models{};
-        models.m = 1;
-        models.la[0] = (const char*)lookahead_emb + (size_t)b0 * h->d_resp[0] * esz;
-        models.emb[0] = h->emb[0];
-        models.d[0] = h->d_resp[0];
-        models.d_pad[0] = h->d_pad_resp[0];
-        models.tau[0] = tau_r;
+        VerifyArgs v{};
+        v.models.m = 1;
+        v.models.la[0] = (const char*)lookahead_emb + (size_t)b0 * h->d_resp[0] * esz;
+        v.models.emb[0] = h->emb[0];
+        v.models.d[0] = h->d_resp[0];
+        v.models.d_pad[0] = h->d_pad_resp[0];
+        v.models.tau[0] = tau_r;
+        v.la_tok = lookahead_tokens + (size_t)b0 * k;
+        v.k = k;
+        v.tokens = h->tokens;
+        v.k_cap = h->k_cap;
+        v.tau_q = tau_q;
+        v.idx = idx + b0;
+        v.score = score + b0;
+        v.resp_score = resp_score + b0;
+        v.decision = decision + b0;
         if (launch_lsh_lookup(q, h->dtype, nb, h->d, h->d_pad, h->qt, h->hp, h->lsh_bits, h->sigq, h->keys, h->sig,
-                              h->size, radius, h->lsh_max_cand, h->lsh_cnt, h->lsh_cand, n_cand + b0, models,
-                              lookahead_tokens + (size_t)b0 * k, k, h->tokens, h->k_cap, tau_q, idx + b0,
-                              score + b0, resp_score + b0, decision + b0, h->num_cu, s) != hipSuccess)
+                              h->size, radius, h->lsh_max_cand, h->lsh_cnt, h->lsh_cand, n_cand + b0, v, h->num_cu,
+                              s) != hipSuccess)
             return LACACHE_EHIP;
     }
     return LACACHE_OK;

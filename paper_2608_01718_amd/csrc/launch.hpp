@@ -60,16 +60,44 @@ hipError_t launch_normalise(const void* in, int dtype, int64_t rows, int64_t row
 hipError_t launch_export(const uint16_t* src, int64_t first, int n, int d, int d_pad, uint16_t* dst, bool tiled,
                          hipStream_t s);
 
+// The response-prefix embedding models of stage 2 (one per lookahead check of an ensemble).
+constexpr int kMaxModels = 8;
+struct PrefixModels {
+    int m;                             // number of models, 1 .. kMaxModels
+    const void* la[kMaxModels];        // [B][d_i] lookahead embeddings of the batch (cache dtype)
+    const uint16_t* emb[kMaxModels];   // [capacity][d_pad_i] stored normalised prefix embeddings
+    int d[kMaxModels], d_pad[kMaxModels];
+    float tau[kMaxModels];             // stage-2 threshold of each model
+};
+
+// What the end of a lookup needs besides the stage-1 candidates: stage 2's inputs and the outputs of the batch.
+struct VerifyArgs {
+    PrefixModels models;
+    const int32_t* la_tok;   // [B][k]
+    int k;
+    const int32_t* tokens;   // [capacity][k_cap]
+    int k_cap;
+    float tau_q;
+    int32_t* idx;
+    float* score;
+    float* resp_score;       // [B][models.m]
+    int32_t* decision;
+};
+
 // Stage 1, bandwidth-bound path: queries qt (tiled; up to 16 * stream_max_qg rows as one group, zero-padded to
 // a multiple of 16, or up to four such groups, zero-padded to whole groups) against n_rows tiled keys.  Writes, for every query b
 // and every workgroup p of the launch, the packed top-1 candidate
 // part[b * P + p] (P <= kMaxPartials).  Returns the number of partials P through *P_out.
 // With events e0 / e1 the kernel's run time is recorded into them (launch_timed).  With qraw (the caller's
 // [B][d] query rows, dtype 0 f32 / 1 bf16) the kernel normalises the queries itself and qt is not read; this
-// takes d_pad <= 2048 (stream_fused_ncq(d_pad) > 0).
+// takes d_pad <= 2048 (stream_fused_ncq(d_pad) > 0) and B <= 32.  With `verify` too (B <= 32) the workgroup that
+// ends last also merges the partials and runs stage 2, so no launch follows; done: kDoneWords words, zero
+// between launches (the kernel leaves them so).
+constexpr int kDoneWords = 9 * 32;
 hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B, int n_rows, int d_pad,
                                 uint64_t* part, int num_cu, int* P_out, hipStream_t s, hipEvent_t e0 = nullptr,
-                                hipEvent_t e1 = nullptr, const void* qraw = nullptr, int dtype = 0, int d = 0);
+                                hipEvent_t e1 = nullptr, const void* qraw = nullptr, int dtype = 0, int d = 0,
+                                const VerifyArgs* verify = nullptr, uint32_t* done = nullptr);
 int stream_fused_ncq(int d_pad);
 
 // Stage 1, compute-bound path (matrix-core GEMM with a fused row maximum): queries qt (tiled, rows zero-padded
@@ -83,24 +111,12 @@ hipError_t launch_stage1_gemm(const uint16_t* keys, const uint16_t* qt, int B, i
                               uint64_t* part, int num_cu, int* P_out, hipStream_t s, hipEvent_t e0 = nullptr,
                               hipEvent_t e1 = nullptr);
 
-// The response-prefix embedding models of stage 2 (one per lookahead check of an ensemble).
-constexpr int kMaxModels = 8;
-struct PrefixModels {
-    int m;                             // number of models, 1 .. kMaxModels
-    const void* la[kMaxModels];        // [B][d_i] lookahead embeddings of the batch (cache dtype)
-    const uint16_t* emb[kMaxModels];   // [capacity][d_pad_i] stored normalised prefix embeddings
-    int d[kMaxModels], d_pad[kMaxModels];
-    float tau[kMaxModels];             // stage-2 threshold of each model
-};
-
 // Merge the P partial candidates of each query (rows, or 16-row groups to replay against keys_tiled and
 // the tiled queries qt), threshold, and run stage 2 on hits.  resp_score is [B][models.m].  Every query whose
 // group replay does not reproduce its stage-1 score adds 1 to *fallbacks (device memory).
 hipError_t launch_finalize_verify(const uint64_t* part, int P, bool part_groups, const uint16_t* keys_tiled,
-                                  const uint16_t* qt, int B, int n_rows, int dtype, int d_keys,
-                                  const PrefixModels& models, const int32_t* la_tok, int k, const int32_t* tokens,
-                                  int k_cap, float tau_q, int32_t* idx, float* score, float* resp_score,
-                                  int32_t* decision, uint32_t* fallbacks, hipStream_t s);
+                                  const uint16_t* qt, int B, int n_rows, int dtype, int d_keys, const VerifyArgs& v,
+                                  uint32_t* fallbacks, hipStream_t s);
 
 // Threshold calibration over n pairs (a[j], b[j]) of d-dimensional input vectors: sims[j] = the lookup's
 // cosine of the pair; tau[0] = the percentile (linear between the closest ranks), tau[1] = min(cap, tau[0]).
@@ -129,9 +145,7 @@ hipError_t launch_simhash(const uint16_t* rows_tiled, int d_pad, int64_t row0, i
 hipError_t launch_lsh_lookup(const void* queries, int dtype, int nb, int d, int d_pad, uint16_t* qt,
                              const uint16_t* hp_tiled, int bits, uint32_t* sigq, const uint16_t* keys_tiled,
                              const uint32_t* sig_keys, int64_t n_rows, int radius, int max_cand, uint32_t* cnt,
-                             int32_t* cand, int32_t* n_cand, const PrefixModels& models, const int32_t* la_tok,
-                             int k, const int32_t* tokens, int k_cap, float tau_q, int32_t* idx, float* score,
-                             float* resp_score, int32_t* decision, int num_cu, hipStream_t s);
+                             int32_t* cand, int32_t* n_cand, const VerifyArgs& v, int num_cu, hipStream_t s);
 
 // Most partials a stage-1 launch may write per query.
 constexpr int kMaxPartials = 1024;

@@ -108,10 +108,16 @@ __device__ inline int32_t replay_group16(const u32x4* __restrict__ keys, const u
 // One wave: outputs of query b for the packed stage-1 result m (0: no candidate) naming entry i with raw
 // score s_raw.
 __device__ inline void verify_query(int b, uint64_t m, int32_t i, float s_raw, int n_rows, int dtype,
-                                    const PrefixModels& M, const int32_t* __restrict__ la_tok, int k,
-                                    const int32_t* __restrict__ tokens, int k_cap, float tau_q,
-                                    int32_t* __restrict__ idx_out, float* __restrict__ score_out,
-                                    float* __restrict__ resp_out, int32_t* __restrict__ dec_out, int lane) {
+                                    const VerifyArgs& v, int lane) {
+    const PrefixModels& M = v.models;
+    const int32_t* __restrict__ la_tok = v.la_tok;
+    const int32_t* __restrict__ tokens = v.tokens;
+    int32_t* __restrict__ idx_out = v.idx;
+    float* __restrict__ score_out = v.score;
+    float* __restrict__ resp_out = v.resp_score;
+    int32_t* __restrict__ dec_out = v.decision;
+    const int k = v.k, k_cap = v.k_cap;
+    const float tau_q = v.tau_q;
     const float qnan = __uint_as_float(0x7FC00000u);
     const float score = fminf(fmaxf(s_raw, -1.0f), 1.0f);
     // every stored row yields a candidate, so m != 0 here; the range check keeps the gathers in bounds regardless

@@ -377,6 +377,36 @@ def test_determinism_and_paths_agree(lc, B):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("m", [1, 3])
+@pytest.mark.parametrize("N,d", [(1, 64), (255, 384), (257, 768), (2100, 1500), (70_000, 384), (300_001, 128)])
+def test_small_call_in_one_launch_matches_the_gemm_path(lc, N, d, m):
+    """Calls whose last workgroup also ends the lookup (up to 32 queries, 16 with several prefix models; one, two
+    and fewer or more than eight workgroups): bit-equal to the GEMM path and its own finalize launch, on
+    repeated calls and on batch sizes around the limits."""
+    import torch
+    g = torch.Generator().manual_seed(N + d + m)
+    keys = torch.randn((N, d), generator=g).to(torch.bfloat16).cuda()
+    tok = torch.randint(50, (N, 9), generator=g, dtype=torch.int32).cuda()
+    dims = [d] + [96] * (m - 1)
+    embs = [torch.randn((N, x), generator=g).to(torch.bfloat16).cuda() for x in dims]
+    c = lc.LaCache(N, d, 9, lc.BF16, 64, 0, d_resp=dims)
+    c.insert_ensemble(keys, embs, tok)
+    for B in (1, 15, 16, 17, 31, 32, 33):
+        rows = torch.randint(N, (B,), generator=g).cuda()
+        q = (keys[rows].float() + 0.3 * torch.randn((B, d), generator=g).cuda()).to(torch.bfloat16)
+        las = [torch.where(torch.rand((B, 1), generator=g).cuda() < 0.5, e[rows], e[0]) for e in embs]
+        u = torch.where(torch.rand((B, 1), generator=g).cuda() < 0.5, tok[rows], tok[0])
+        c.set_small_batch(0)
+        want = [t.clone() for t in c.lookup_ensemble(q, las, u, 0.9, [0.5] * m, 9)]
+        c.set_small_batch(64)
+        for _ in range(3):
+            got = c.lookup_ensemble(q, las, u, 0.9, [0.5] * m, 9)
+            for a, b in zip(got, want):
+                assert torch.equal(a.view(torch.int32), b.view(torch.int32)), (B, a, b)
+    assert c.replay_fallbacks() == 0
+    c.close()
+
+
 def test_calls_enqueued_on_side_streams(lc):
     """Inserts and lookups of two independent caches enqueued on two side streams (default priority), with no
     host synchronisation between the calls: a lookup sees every insert enqueued before it on its stream, and
