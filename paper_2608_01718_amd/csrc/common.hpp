@@ -267,18 +267,65 @@ __device__ inline void normalise_row(const void* row, int dtype, int d, int d_pa
 }
 
 // A row held in registers: lane l keeps columns l*8 + 512 c .. +7 for c < NC (zeros beyond d, and for rows that
-// are not live), the columns row_norm and quantise8 give lane l.
+// are not live), the columns row_norm and quantise8 give lane l.  Loading is split in two so that a caller can
+// have several rows on their way before it waits for the first: rows of whole 16-byte chunks are loaded without
+// branches (lanes past the row read its first chunk and drop it); others element by element in the second half.
 template <int NC>
-__device__ __forceinline__ void row_to_regs(const char* src, int dtype, int d, bool live, int lane, float (&x)[NC][8]) {
+struct RawRow {
+    u32x4 lo[NC], hi[NC];  // 16-byte pieces: lo alone for a chunk of bfloat16, both for one of float32
+};
+__device__ __forceinline__ bool row_is_chunked(const char* src, int d) {
+    return ((uintptr_t)src & 15) == 0 && d % 8 == 0;
+}
+template <int NC, bool NT = false>
+__device__ __forceinline__ void row_load(const char* src, int dtype, int d, bool live, int lane, RawRow<NC>& r) {
+    const bool any = live && row_is_chunked(src, d);
+    auto at = [&](int c, int half) {
+        const int j0 = lane * 8 + 512 * c;
+        const u32x4* p = (const u32x4*)(src + (j0 < d ? (size_t)j0 * (dtype == 0 ? 4 : 2) + 16 * half : 0));
+        return NT ? __builtin_nontemporal_load(p) : *p;
+    };
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        if (live) {
-            load8f(src, dtype, d, lane * 8 + 512 * c, x[c]);
-        } else {
+    for (int c = 0; c < NC; ++c) r.lo[c] = any ? at(c, 0) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[c][e] = 0.0f;
+    for (int c = 0; c < NC; ++c) r.hi[c] = any && dtype == 0 ? at(c, 1) : u32x4{0u, 0u, 0u, 0u};
+}
+template <int NC>
+__device__ __forceinline__ void row_unpack(const char* src, int dtype, int d, bool live, int lane, const RawRow<NC>& r,
+                                           float (&x)[NC][8]) {
+    if (live && !row_is_chunked(src, d)) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) load8f(src, dtype, d, lane * 8 + 512 * c, x[c]);
+        return;
+    }
+    if (dtype == 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const bool in = lane * 8 + 512 * c < d;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                x[c][t] = __uint_as_float(in ? r.lo[c][t] : 0u);
+                x[c][4 + t] = __uint_as_float(in ? r.hi[c][t] : 0u);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const bool in = lane * 8 + 512 * c < d;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t u = in ? r.lo[c][t] : 0u;
+                x[c][2 * t] = __uint_as_float(u << 16);
+                x[c][2 * t + 1] = __uint_as_float(u & 0xFFFF0000u);
+            }
         }
     }
+}
+template <int NC>
+__device__ __forceinline__ void row_to_regs(const char* src, int dtype, int d, bool live, int lane, float (&x)[NC][8]) {
+    RawRow<NC> r;
+    row_load<NC>(src, dtype, d, live, lane, r);
+    row_unpack<NC>(src, dtype, d, live, lane, r, x);
 }
 
 // Its norm, the squares summed in the order row_norm uses (the zeros it skips add nothing), so the two agree
@@ -293,17 +340,67 @@ __device__ __forceinline__ double regs_norm(const float (&x)[NC][8]) {
     return __builtin_sqrt(wave_sum_f64(ss));
 }
 
-// Columns j0 .. j0+7 of the row in registers (x = its c-th piece) rounded as quantise8 rounds them.
-__device__ __forceinline__ u32x4 regs_quantise8(const float (&x)[8], int j0, int d, double n, float rnf, bool live) {
-    uint32_t h[8];
+// The row divided by its norm and rounded to bfloat16, two values to a word, as bf16_rne_quotient rounds each:
+// the float32 products are rounded in pairs, and a lane with a product that the proof of bf16_rne_quotient_fast
+// does not cover (within 2 units of a rounding midpoint, or below 2^-125) goes through the division for it.
+// One element in 13,000 is such a one, 7 % of 1024-column rows hold any, so the test is made once per row and
+// the loop over a lane's elements is left out of the common path (with a branch per element, bulk inserts of
+// 1024-column prefix rows stored 131,000 of them in 79 us; 65 us so).  A zero norm gives zeros.  The whole wave
+// calls it, with one n for all lanes; rnf = quotient_rcp_f32(n).
+template <int NC>
+__device__ __forceinline__ void quantise_row(const float (&x)[NC][8], double n, float rnf, int d, int lane,
+                                             uint32_t (&p)[NC * 4]) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    constexpr uint32_t kTiny = 0x01000000u;  // bits of 2^-125
+    if (n == 0.0) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) h[e] = (live && j0 + e < d && n != 0.0) ? bf16_rne_quotient(x[e], n, rnf) : 0u;
-    u32x4 w;
-    w.x = h[0] | (h[1] << 16);
-    w.y = h[2] | (h[3] << 16);
-    w.z = h[4] | (h[5] << 16);
-    w.w = h[6] | (h[7] << 16);
-    return w;
+        for (int k = 0; k < NC * 4; ++k) p[k] = 0u;
+        return;
+    }
+    uint16_t window = 0xFFFFu;
+    float least = __builtin_inff();
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        float low = __builtin_inff();
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float f0 = x[c][2 * t] * rnf, f1 = x[c][2 * t + 1] * rnf;
+            const uint16_t w0 = (uint16_t)(__float_as_uint(f0) - 0x7FFEu);
+            const uint16_t w1 = (uint16_t)(__float_as_uint(f1) - 0x7FFEu);
+            window = w0 < window ? w0 : window;
+            window = w1 < window ? w1 : window;
+            low = fminf(fminf(__builtin_fabsf(f0), __builtin_fabsf(f1)), low);
+            p[c * 4 + t] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{f0, f1}), bf16x2));
+        }
+        if (lane * 8 + 512 * c < d) least = fminf(least, low);
+    }
+    if (__ballot(window <= 4u || least < __uint_as_float(kTiny)) == 0ull) return;
+    __asm__ volatile("" : "+v"(rnf));  // form the products again rather than keep them all for this rare path
+    uint32_t todo = 0u;  // the lane's elements that need the division (zeros are exact as they are)
+#pragma unroll
+    for (int i = 0; i < NC * 8; ++i) {
+        const float v = x[i >> 3][i & 7];
+        const uint32_t u = __float_as_uint(v * rnf);
+        if ((u & 0xFFFFu) - 0x7FFEu <= 4u || ((u & 0x7FFFFFFFu) < kTiny && v != 0.0f)) todo |= 1u << i;
+    }
+    while (__ballot(todo != 0u) != 0ull) {
+        const int i = todo != 0u ? __ffs(todo) - 1 : NC * 8;
+        float v = 0.0f;
+#pragma unroll
+        for (int k = 0; k < NC * 8; ++k) v = k == i ? x[k >> 3][k & 7] : v;
+        const uint32_t h = bf16_rne_from_f64((double)v / n);
+#pragma unroll
+        for (int k = 0; k < NC * 4; ++k)
+            if (k == i >> 1) p[k] = (i & 1) ? (p[k] & 0xFFFFu) | (h << 16) : (p[k] & 0xFFFF0000u) | h;
+        todo &= todo - 1u;
+    }
+}
+
+// The 8 values of chunk c.
+template <int N>
+__device__ __forceinline__ u32x4 piece(const uint32_t (&p)[N], int c) {
+    return u32x4{p[4 * c], p[4 * c + 1], p[4 * c + 2], p[4 * c + 3]};
 }
 
 // Dot product of two packed bfloat16 chunks, accumulated into acc in float32 in column order.  bf16 x bf16

@@ -28,102 +28,6 @@ __constant__ const int kBits[kPasses] = {11, 11, 10};
 
 }  // namespace
 
-// The elements of a row in registers: lane l keeps columns 8 l + 512 c .. + 7 for c < NC, zeros beyond d.  Rows of
-// whole 16-byte chunks (fast) are loaded without branches, every load issued before the first is used, and
-// non-temporally (each row is read once); others element by element.
-template <int NC>
-__device__ __forceinline__ void load_pair(const char* ra, const char* rb, int dtype, int d, bool fast, int lane,
-                                          float (&xa)[NC][8], float (&xb)[NC][8]) {
-    if (!fast) {
-        row_to_regs<NC>(ra, dtype, d, true, lane, xa);
-        row_to_regs<NC>(rb, dtype, d, true, lane, xb);
-        return;
-    }
-    auto at = [&](const char* r, int c, int half) {  // lanes past the row read its first chunk, and drop it
-        const int j0 = lane * 8 + 512 * c;
-        const size_t off = j0 < d ? (size_t)j0 * (dtype == 0 ? 4 : 2) + 16 * half : 0;
-        return __builtin_nontemporal_load((const u32x4*)(r + off));
-    };
-    if (dtype == 0) {
-        u32x4 a[NC][2], b[NC][2];
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) a[c][h] = at(ra, c, h), b[c][h] = at(rb, c, h);
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const bool in = lane * 8 + 512 * c < d;
-                xa[c][e] = in ? __uint_as_float(a[c][e >> 2][e & 3]) : 0.0f;
-                xb[c][e] = in ? __uint_as_float(b[c][e >> 2][e & 3]) : 0.0f;
-            }
-    } else {
-        u32x4 a[NC], b[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) a[c] = at(ra, c, 0), b[c] = at(rb, c, 0);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const bool in = lane * 8 + 512 * c < d;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint32_t u = in ? a[c][t] : 0u, v = in ? b[c][t] : 0u;
-                xa[c][2 * t] = __uint_as_float(u << 16), xa[c][2 * t + 1] = __uint_as_float(u & 0xFFFF0000u);
-                xb[c][2 * t] = __uint_as_float(v << 16), xb[c][2 * t + 1] = __uint_as_float(v & 0xFFFF0000u);
-            }
-        }
-    }
-}
-
-// The row divided by its norm and rounded to bfloat16, two values to a word, as bf16_rne_quotient rounds each:
-// the float32 products are rounded in pairs, and a lane with a product that the proof of bf16_rne_quotient_fast
-// does not cover (within 2 units of a rounding midpoint, or below 2^-125) goes through the division for it.
-// One element in 13,000 is such a one, 7 % of 1024-column rows hold any, so the test is made once per row and
-// the loop over a lane's elements is left out of the common path.  rnf = quotient_rcp_f32(n).
-template <int NC>
-__device__ __forceinline__ void quantise_row(const float (&x)[NC][8], double n, float rnf, int d, int lane,
-                                             uint32_t (&p)[NC * 4]) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    constexpr uint32_t kTiny = 0x01000000u;  // bits of 2^-125
-    uint16_t window = 0xFFFFu;
-    float least = __builtin_inff();
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        float low = __builtin_inff();
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const float f0 = x[c][2 * t] * rnf, f1 = x[c][2 * t + 1] * rnf;
-            const uint16_t w0 = (uint16_t)(__float_as_uint(f0) - 0x7FFEu);
-            const uint16_t w1 = (uint16_t)(__float_as_uint(f1) - 0x7FFEu);
-            window = w0 < window ? w0 : window;
-            window = w1 < window ? w1 : window;
-            low = fminf(fminf(__builtin_fabsf(f0), __builtin_fabsf(f1)), low);
-            p[c * 4 + t] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{f0, f1}), bf16x2));
-        }
-        if (lane * 8 + 512 * c < d) least = fminf(least, low);
-    }
-    if (__ballot(window <= 4u || least < __uint_as_float(kTiny)) == 0ull) return;
-    uint32_t todo = 0u;  // the lane's elements that need the division (zeros are exact as they are)
-#pragma unroll
-    for (int i = 0; i < NC * 8; ++i) {
-        const float v = x[i >> 3][i & 7];
-        const uint32_t u = __float_as_uint(v * rnf);
-        if ((u & 0xFFFFu) - 0x7FFEu <= 4u || ((u & 0x7FFFFFFFu) < kTiny && v != 0.0f)) todo |= 1u << i;
-    }
-    while (__ballot(todo != 0u) != 0ull) {
-        const int i = todo != 0u ? __ffs(todo) - 1 : NC * 8;
-        float v = 0.0f;
-#pragma unroll
-        for (int k = 0; k < NC * 8; ++k) v = k == i ? x[k >> 3][k & 7] : v;
-        const uint32_t h = bf16_rne_from_f64((double)v / n);
-#pragma unroll
-        for (int k = 0; k < NC * 4; ++k)
-            if (k == i >> 1) p[k] = (i & 1) ? (p[k] & 0xFFFFu) | (h << 16) : (p[k] & 0xFFFF0000u) | h;
-        todo &= todo - 1u;
-    }
-}
-
 // One wave per pair: normalise a[j] and b[j] as stored vectors are, and dot the rounded values in column order per
 // lane, then across the wave (products of two bfloat16 values are exact in float32).  NC > 0: d <= 512 NC and each
 // lane keeps its 8 NC columns of both rows in registers, read once; the norms are summed in the order row_norm
@@ -132,7 +36,7 @@ __device__ __forceinline__ void quantise_row(const float (&x)[NC][8], double n, 
 // NC = 0: any d, the rows read once for the norms and once for the dot.
 template <int NC>
 __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const void* __restrict__ b, int dtype, int d,
-                                            bool fast, int64_t j, float* __restrict__ sims) {
+                                            int64_t j, float* __restrict__ sims) {
     const int lane = threadIdx.x & 63;
     const size_t esz = dtype == 0 ? 4 : 2;
     const char* ra = (const char*)a + j * d * esz;
@@ -140,7 +44,11 @@ __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const vo
     float acc = 0.0f;
     if constexpr (NC > 0) {
         float xa[NC][8], xb[NC][8];
-        load_pair<NC>(ra, rb, dtype, d, fast, lane, xa, xb);
+        RawRow<NC> wa, wb;  // non-temporal: each row is read once
+        row_load<NC, true>(ra, dtype, d, true, lane, wa);
+        row_load<NC, true>(rb, dtype, d, true, lane, wb);
+        row_unpack<NC>(ra, dtype, d, true, lane, wa, xa);
+        row_unpack<NC>(rb, dtype, d, true, lane, wb, xb);
         double sa = 0.0, sb = 0.0;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -204,13 +112,12 @@ __global__ __launch_bounds__(256) void k_pair_cosine(const void* __restrict__ a,
                                                      uint32_t* __restrict__ state, uint32_t* __restrict__ hist,
                                                      uint32_t r0, uint32_t r1) {
     if (blockIdx.x == 0) select_init(state, hist, r0, r1);
-    const bool fast = (((uintptr_t)a | (uintptr_t)b) & 15) == 0 && d % 8 == 0;  // every row 16-byte aligned
     const int64_t j0 = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (LOOP) {
-        for (int64_t j = j0; j < n; j += (int64_t)gridDim.x * 4) pair_cosine<NC>(a, b, dtype, d, fast, j, sims);
+        for (int64_t j = j0; j < n; j += (int64_t)gridDim.x * 4) pair_cosine<NC>(a, b, dtype, d, j, sims);
     } else {
         if (j0 >= n) return;
-        pair_cosine<NC>(a, b, dtype, d, fast, j0, sims);
+        pair_cosine<NC>(a, b, dtype, d, j0, sims);
     }
 }
 

@@ -306,12 +306,13 @@ __global__ __launch_bounds__(1024) void k_lsh_prep(const void* __restrict__ quer
         float x[NC][8];
         row_to_regs<NC>(src, dtype, d, live, lane, x);
         const double n = regs_norm<NC>(x);
-        const float rnf = quotient_rcp_f32(n);
+        uint32_t z[NC * 4];
+        quantise_row<NC>(x, n, quotient_rcp_f32(n), d, lane, z);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             const int j0 = lane * 8 + 512 * c, J = j0 >> 3;
             if (j0 < d_pad) {
-                const u32x4 w = regs_quantise8(x[c], j0, d, n, rnf, live);
+                const u32x4 w = piece(z, c);
                 *(u32x4*)(qt + tiled_offset(r, j0, kc)) = w;
                 qs[(J >> 2) * 64 + (J & 3) * 16 + wv] = w;
             }

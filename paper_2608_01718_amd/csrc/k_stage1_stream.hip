@@ -86,15 +86,13 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
 #pragma unroll
             for (int t = 0; t < kAhead; ++t) {
                 const int q = q0 + t;
-                const bool live = ((int64_t)h * QG + q) * 16 + wid < B;
                 const double n = regs_norm<NCQ>(x[t]);
-                const float rnf = quotient_rcp_f32(n);
+                uint32_t z[NCQ * 4];
+                quantise_row<NCQ>(x[t], n, quotient_rcp_f32(n), d, lane, z);
 #pragma unroll
                 for (int c = 0; c < NCQ; ++c) {
                     const int j0 = lane * 8 + 512 * c, J = j0 >> 3;
-                    if (j0 < kc * 32)
-                        qs[(q * kc + (J >> 2)) * 64 + (J & 3) * 16 + wid] =
-                            regs_quantise8(x[t][c], j0, d, n, rnf, live);
+                    if (j0 < kc * 32) qs[(q * kc + (J >> 2)) * 64 + (J & 3) * 16 + wid] = piece(z, c);
                 }
             }
         }

@@ -120,6 +120,23 @@ int alloc_zero(void** p, size_t bytes) {
     return hipMemset(*p, 0, bytes) == hipSuccess ? LACACHE_OK : LACACHE_EHIP;
 }
 
+// The store as the source of an export, no outputs set.
+EntryArrays store_arrays(lacache_s* h) {
+    EntryArrays a{};
+    a.keys = h->keys;
+    a.d = h->d;
+    a.d_pad = h->d_pad;
+    a.m = h->m;
+    for (int i = 0; i < h->m; ++i) {
+        a.emb[i] = h->emb[i];
+        a.d_resp[i] = h->d_resp[i];
+        a.d_pad_resp[i] = h->d_pad_resp[i];
+    }
+    a.tokens = h->tokens;
+    a.k_cap = h->k_cap;
+    return a;
+}
+
 void clear_prof(lacache_s* h) { h->prof_used = 0; }
 
 // Makes sure at least n event pairs exist.
@@ -248,15 +265,16 @@ int lacache_insert_ensemble(lacache_t h, const void* keys, const void* const* re
     if (!g.ok) return LACACHE_EHIP;
     hipStream_t s = (hipStream_t)stream;
     const int64_t first = h->size;
-    if (launch_normalise(keys, h->dtype, n, n, h->d, h->d_pad, h->keys, first, true, s) != hipSuccess)
-        return LACACHE_EHIP;
-    for (int i = 0; i < h->m; ++i)
-        if (launch_normalise(resp_emb[i], h->dtype, n, n, h->d_resp[i], h->d_pad_resp[i], h->emb[i], first, false,
-                             s) != hipSuccess)
-            return LACACHE_EHIP;
-    if (hipMemcpyAsync(h->tokens + first * h->k_cap, resp_tokens, (size_t)n * h->k_cap * 4,
-                       hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return LACACHE_EHIP;
+    EntryArrays a = store_arrays(h);
+    a.keys = keys;
+    a.keys_out = h->keys;
+    for (int i = 0; i < h->m; ++i) {
+        a.emb[i] = resp_emb[i];
+        a.emb_out[i] = h->emb[i];
+    }
+    a.tokens = resp_tokens;
+    a.tokens_out = h->tokens;
+    if (launch_insert(a, h->dtype, n, first, s) != hipSuccess) return LACACHE_EHIP;
     if (h->lsh_bits &&
         launch_simhash(h->keys, h->d_pad, first, n, h->hp, h->lsh_bits, h->sig, h->num_cu, s) != hipSuccess)
         return LACACHE_EHIP;
@@ -367,14 +385,13 @@ int lacache_export(lacache_t h, int64_t first, int32_t n, uint16_t* keys_bf16, u
     DeviceGuard g(h->device);
     if (!g.ok) return LACACHE_EHIP;
     hipStream_t s = (hipStream_t)stream;
-    if (keys_bf16 && launch_export(h->keys, first, n, h->d, h->d_pad, keys_bf16, true, s) != hipSuccess)
-        return LACACHE_EHIP;
-    if (emb_bf16 && launch_export(h->emb[0], first, n, h->d_resp[0], h->d_pad_resp[0], emb_bf16, false, s) !=
-                        hipSuccess)
-        return LACACHE_EHIP;
-    if (tokens && hipMemcpyAsync(tokens, h->tokens + first * h->k_cap, (size_t)n * h->k_cap * 4,
-                                 hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return LACACHE_EHIP;
+    if (!keys_bf16 && !emb_bf16 && !tokens) return LACACHE_OK;
+    EntryArrays a = store_arrays(h);
+    a.m = 1;
+    a.keys_out = keys_bf16;
+    a.emb_out[0] = emb_bf16;
+    a.tokens_out = tokens;
+    if (launch_export(a, first, n, s) != hipSuccess) return LACACHE_EHIP;
     return LACACHE_OK;
 }
 
@@ -384,9 +401,13 @@ int lacache_export_prefix(lacache_t h, int32_t model, int64_t first, int32_t n, 
     if (!emb_bf16) return LACACHE_EINVAL;
     DeviceGuard g(h->device);
     if (!g.ok) return LACACHE_EHIP;
-    if (launch_export(h->emb[model], first, n, h->d_resp[model], h->d_pad_resp[model], emb_bf16, false,
-                      (hipStream_t)stream) != hipSuccess)
-        return LACACHE_EHIP;
+    EntryArrays a = store_arrays(h);
+    a.m = 1;
+    a.emb[0] = h->emb[model];
+    a.d_resp[0] = h->d_resp[model];
+    a.d_pad_resp[0] = h->d_pad_resp[model];
+    a.emb_out[0] = emb_bf16;
+    if (launch_export(a, first, n, (hipStream_t)stream) != hipSuccess) return LACACHE_EHIP;
     return LACACHE_OK;
 }
 

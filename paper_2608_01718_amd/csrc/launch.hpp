@@ -56,12 +56,30 @@ hipError_t launch_timed(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds,
 hipError_t launch_normalise(const void* in, int dtype, int64_t rows, int64_t rows_pad, int d, int d_pad,
                             uint16_t* out, int64_t row0, bool tiled, hipStream_t s);
 
-// Dense [n][d] copy of stored rows first .. first+n-1.
-hipError_t launch_export(const uint16_t* src, int64_t first, int n, int d, int d_pad, uint16_t* dst, bool tiled,
-                         hipStream_t s);
+// The arrays of an insert or an export: rows of keys (tiled store), of up to kMaxModels prefix-embedding
+// models (row-major stores) and of prefix tokens.  Callers' arrays are dense ([n][d], [n][k_cap]).
+constexpr int kMaxModels = 8;
+struct EntryArrays {
+    const void* keys;                 // caller's rows (insert) or the store (export)
+    uint16_t* keys_out;               // the store (insert) or the caller's rows (export); null: not wanted
+    int d, d_pad;
+    int m;
+    const void* emb[kMaxModels];
+    uint16_t* emb_out[kMaxModels];    // null: not wanted
+    int d_resp[kMaxModels], d_pad_resp[kMaxModels];
+    const int32_t* tokens;
+    int32_t* tokens_out;              // null: not wanted
+    int k_cap;
+};
+
+// Store n entries at rows row0 .. row0+n-1: vectors normalised and rounded to bfloat16, tokens copied (the store's
+// arrays are their bases, not row row0).
+hipError_t launch_insert(const EntryArrays& a, int dtype, int64_t n, int64_t row0, hipStream_t s);
+
+// Dense copies of stored rows first .. first+n-1.
+hipError_t launch_export(const EntryArrays& a, int64_t first, int n, hipStream_t s);
 
 // The response-prefix embedding models of stage 2 (one per lookahead check of an ensemble).
-constexpr int kMaxModels = 8;
 struct PrefixModels {
     int m;                             // number of models, 1 .. kMaxModels
     const void* la[kMaxModels];        // [B][d_i] lookahead embeddings of the batch (cache dtype)

@@ -153,6 +153,7 @@ __device__ inline void verify_query(int b, uint64_t m, int32_t i, float s_raw, i
             // dot order as normalise_row, one wait for memory instead of three
             float x[2][8];
             u32x4 e[2];
+            uint32_t z[8];
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 const int j0 = lane * 8 + 512 * c;
@@ -160,12 +161,10 @@ __device__ inline void verify_query(int b, uint64_t m, int32_t i, float s_raw, i
             }
             row_to_regs<2>(src, dtype, d, true, lane, x);
             const double n = regs_norm<2>(x);
-            const float rnf = quotient_rcp_f32(n);
+            quantise_row<2>(x, n, quotient_rcp_f32(n), d, lane, z);
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const int j0 = lane * 8 + 512 * c;
-                if (j0 < d_pad) acc = dot8_bf16(regs_quantise8(x[c], j0, d, n, rnf, true), e[c], acc);
-            }
+            for (int c = 0; c < 2; ++c)
+                if (lane * 8 + 512 * c < d_pad) acc = dot8_bf16(piece(z, c), e[c], acc);
         } else {
             normalise_row(src, dtype, d, d_pad, true, lane,
                           [&](int j0, u32x4 w) { acc = dot8_bf16(w, er[j0 >> 3], acc); });

@@ -99,6 +99,42 @@ def test_keys_and_prefix_rows_store_identically(lc, N, chunk, d, dtype):
     assert not got[5].any()
 
 
+@pytest.mark.parametrize("dtype", [oracle.F32, oracle.BF16])
+@pytest.mark.parametrize("d,dims,k_cap", [(768, (768,), 16), (100, (33, 2048, 500), 65), (1025, (64,), 1),
+                                          (2049, (384, 16), 150)])
+def test_insert_sizes_store_and_export_alike(lc, d, dims, k_cap, dtype):
+    """Entries inserted a few at a time (one launch per call), starting anywhere in a 16-row group, and all at once
+    (the bulk kernels) are stored alike: every prefix model, the tokens as given, and exports of any row
+    range and of either array alone, into aligned and unaligned buffers."""
+    import torch
+    g = torch.Generator().manual_seed(d)
+    N = 9000
+    cast = lambda t: (t if dtype == oracle.F32 else t.to(torch.bfloat16)).cuda()  # noqa: E731
+    keys, embs = cast(torch.randn((N, d), generator=g)), [cast(torch.randn((N, x), generator=g)) for x in dims]
+    tok = torch.randint(1000, (N, k_cap), generator=g, dtype=torch.int32).cuda()
+    a, b = (lc.LaCache(N, d, k_cap, dtype, 16, 0, d_resp=dims) for _ in range(2))
+    a.insert_ensemble(keys, embs, tok)
+    r0, steps = 0, [1, 15, 16, 17, 3, 100, 31, 8192]
+    while r0 < N:
+        n = min(steps.pop(0) if steps else 200, N - r0)
+        assert b.insert_ensemble(keys[r0:r0 + n], [e[r0:r0 + n] for e in embs], tok[r0:r0 + n]) == r0
+        r0 += n
+    for first, n in ((0, N), (1, 1), (17, 4000)):
+        ka, ea, ta = a.export(first, n)
+        kb, eb, tb = b.export(first, n)
+        assert torch.equal(ka, kb) and torch.equal(ea, eb) and torch.equal(ta, tb)
+        assert torch.equal(ta, tok[first:first + n])
+        for i in range(len(dims)):
+            assert torch.equal(a.export_prefix(i, first, n), b.export_prefix(i, first, n))
+    buf = torch.full((50 * d + 1,), -1, dtype=torch.int16, device="cuda")
+    lib = lc.raw_library()
+    assert lib.lacache_export(a.handle, 7, 50, buf.data_ptr() + 2, None, None, 0) == lc.OK
+    torch.cuda.synchronize()
+    assert torch.equal(buf[1:].view(50, d), a.export(7, 50)[0]) and buf[0] == -1
+    a.close()
+    b.close()
+
+
 def test_single_insert_and_export_beyond_one_grid(lc):
     """One insert of 4.3M rows (more rows than one launch of the normaliser covers: its waves loop) and one
     export of all of them (4.3M x 80 values, more than one launch of the export covers: its threads loop),
