@@ -291,7 +291,8 @@ int lacache_export_signatures(lacache_t h, int64_t first, int32_t n, uint32_t *s
  * Batch-size crossover of stage 1: batches of at most b_small queries use the
  * bandwidth-bound streaming kernel, larger ones the matrix-core GEMM kernel.
  * The streaming kernel runs up to four groups of 64 queries (fewer queries
- * per group for d > 1152).  b_small is -1, or from 0 up to the streaming
+ * per group for d > 1152; 65 to 128 queries of 769 to 1024 columns as one
+ * group).  b_small is -1, or from 0 up to the streaming
  * kernel's largest batch (256 for d <= 1152); anything else is EINVAL.
  * 0 sends every batch to the GEMM kernel.  -1 (the default) lets each call
  * choose from the number of stored entries n and the padded dimension d_pad:

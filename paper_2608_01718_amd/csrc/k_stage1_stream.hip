@@ -196,6 +196,94 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
     }
 }
 
+// The same pass for up to 128 queries: too many for LDS, they live in registers
+// instead, and the keys pass through LDS.  A workgroup is eight waves, two per SIMD; wave w keeps the operand
+// fragments of 16 queries for every column (4 KC registers), and a key is read from memory once for 128 queries.
+// The waves fetch a stage of kG 16-key groups together (as few as eight waves can share), SETS stages ahead in
+// registers, and hand it over through two LDS slots with one barrier per stage.  Bound by HBM and, close behind, by
+// LDS reads (every wave reads every key).  100 queries, whole calls, against two groups of the kernel above:
+// 94 / 105 us on 250k x 1024 keys (5.9 TB/s), 178 / 195 us on 500k x 1024, 65 / 73 us on 150k x 900, 47 / 55 us on
+// 100k x 1024.  Up to 768 columns the two groups, whose waves have less to do per key, are as fast or faster
+// (100k x 768: 44 / 44 us, 100k x 384: 27 / 24 us).  Four waves of 32 queries, one per SIMD, read half as much from
+// LDS but were slower (112 us on 250k x 1024): nothing hides one wave's chain of reads, products and barriers.
+template <int KC, int kG, int SETS>
+__global__ __launch_bounds__(512, 2) void k_stage1_wide(const u32x4* __restrict__ keys, const u32x4* __restrict__ qt,
+                                                        int groups, int n_rows, int n_ranges, int B,
+                                                        uint64_t* __restrict__ part) {
+    constexpr int kLoads = kG * KC / 8;   // chunks a wave fetches per stage
+    static_assert(kG * KC % 8 == 0, "");
+    constexpr int kUnroll = SETS % 2 == 0 ? SETS : 2 * SETS;
+    extern __shared__ u32x4 smem[];       // [2][kG * KC * 64]
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = (int)blockIdx.x;
+    // the range's stages; the last of all may reach one group past the entries, into the store's spare rows
+    const int stages = (groups + kG - 1) / kG;
+    const int s0 = (int)((int64_t)r * stages / n_ranges);
+    const int s1 = (int)((int64_t)(r + 1) * stages / n_ranges);  // > s0: n_ranges <= stages
+
+    u32x4 set[SETS][kLoads];
+    auto fetch = [&](u32x4 (&dst)[kLoads], int t) {  // past the range: its last stage again, not used
+        const u32x4* p = keys + ((int64_t)(t < s1 ? t : s1 - 1) * (kG * KC) + wv) * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) dst[i] = __builtin_nontemporal_load(p + i * 512);
+    };
+    auto publish = [&](int slot, const u32x4 (&src)[kLoads]) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) smem[(slot * kG * KC + wv + 8 * i) * 64 + lane] = src[i];
+    };
+    auto barrier = [&]() {  // orders LDS accesses only: the fetches stay in flight across it
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+#pragma unroll
+    for (int t = 0; t < SETS; ++t) fetch(set[t], s0 + t);
+    u32x4 qf[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) qf[c] = qt[((int64_t)wv * KC + c) * 64 + lane];
+
+    float best = -__builtin_inff();
+    int bidx = 0x7FFFFFFF;
+    publish(0, set[0]);
+    fetch(set[0], s0 + SETS);
+    barrier();
+    for (int t = s0; t < s1; t += kUnroll) {
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            if (t + u >= s1) break;
+            publish((u + 1) & 1, set[(u + 1) % SETS]);
+            fetch(set[(u + 1) % SETS], t + u + 1 + SETS);
+            f32x4 acc[kG];
+#pragma unroll
+            for (int g = 0; g < kG; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const u32x4* k = smem + (u & 1) * kG * KC * 64 + lane;
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+#pragma unroll
+                for (int g = 0; g < kG; ++g) acc[g] = mfma16x16x32(k[(g * KC + c) * 64], qf[c], acc[g]);
+#pragma unroll
+            for (int g = 0; g < kG; ++g) {
+                const int row0 = ((t + u) * kG + g) * 16 + 4 * (lane >> 4);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float s = acc[g][j];
+                    if (row0 + j < n_rows && s > best) {
+                        best = s;
+                        bidx = row0 + j;
+                    }
+                }
+            }
+            barrier();
+        }
+    }
+    uint64_t p = bidx == 0x7FFFFFFF ? 0ull : pack_top1(best, bidx);
+    p = xor_combine<16>(p, umax64);
+    p = xor_combine<32>(p, umax64);
+    const int q = wv * 16 + lane;
+    if (lane < 16 && q < B) part[(int64_t)q * n_ranges + r] = p;
+}
+
 // Arguments of one streaming launch.
 struct StreamLaunch {
     const u32x4* keys;
@@ -278,6 +366,32 @@ hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B,
         case 2: return single ? launch_qg<2, true>(a) : launch_qg<2, false>(a);
         case 3: return single ? launch_qg<3, true>(a) : launch_qg<3, false>(a);
         default: return single ? launch_qg<4, true>(a) : launch_qg<4, false>(a);
+    }
+}
+
+template <int KC>
+static hipError_t launch_wide(const uint16_t* k, const uint16_t* q, int n_rows, int B, uint64_t* part, int num_cu,
+                              int* P_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const u32x4 *keys = (const u32x4*)k, *qt = (const u32x4*)q;
+    const int groups = (n_rows + 15) / 16;
+    constexpr int kG = KC % 8 == 0 ? 1 : 2, kSets = kG == 1 ? 4 : 2;  // what 256 registers hold beside the queries
+    constexpr int kLds = 2 * kG * KC * 1024;
+    const int stages = (groups + kG - 1) / kG, n_ranges = stages < num_cu ? stages : num_cu;
+    *P_out = n_ranges;
+    static std::atomic<uint64_t> allowed{0};
+    const hipError_t e = allow_dynamic_lds((const void*)k_stage1_wide<KC, kG, kSets>, kLds, allowed);
+    if (e != hipSuccess) return e;
+    return launch_timed(k_stage1_wide<KC, kG, kSets>, dim3(n_ranges), dim3(512), kLds, s, e0, e1, keys, qt, groups,
+                        n_rows, n_ranges, B, part);
+}
+
+hipError_t launch_stage1_wide(const uint16_t* keys, const uint16_t* qt, int B, int n_rows, int d_pad, uint64_t* part,
+                              int num_cu, int* P_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (n_rows <= 0 || B < 1 || B > kWideQueries || num_cu < 1) return hipErrorInvalidValue;
+    switch (d_pad) {
+        case 896: return launch_wide<28>(keys, qt, n_rows, B, part, num_cu, P_out, s, e0, e1);
+        case 1024: return launch_wide<32>(keys, qt, n_rows, B, part, num_cu, P_out, s, e0, e1);
+        default: return hipErrorInvalidValue;
     }
 }
 

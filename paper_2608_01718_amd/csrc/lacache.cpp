@@ -19,6 +19,7 @@ int stream_max_batch(int d_pad);
 // - 1M x 768, 1M x 1024 and 500k x 2048 keys: the GEMM kernel wins as soon as a second query group is
 //   needed (by 3-6 % against two groups, up to 24 % against three or four);
 // - 300k x 1536: two streaming groups still win (by 6 %), three lose (by 24 %);
+// - 500k x 1024: the wide form of the streaming kernel wins up to 128 queries (by 7-12 %), on 1M x 1024 it is even;
 // - 100k x 768: three streaming groups win (by 11-15 %), four lose.
 // Each added group costs the streaming kernel a share of the contraction on every CU, while the GEMM
 // kernel's time for one or two query tiles is its pass over the keys; the fewer the keys, the longer the
@@ -294,10 +295,11 @@ static int lookup_chunk(lacache_t h, const char* queries, int B, const VerifyArg
     int P = 0;
     const bool small = B <= (h->b_small >= 0 ? h->b_small : stream_auto_batch(h->d_pad, n_rows));
     if (n_rows > 0) {
-        // the streaming kernel runs more than one query group on whole groups of 16 * stream_max_qg rows
+        // the streaming kernel runs more than one query group on whole groups of 16 * stream_max_qg rows; 65 to 128
+        // queries of 769 to 1024 columns take the wide kernel instead, which reads the keys once for all of them
         const int64_t grp = 16 * (int64_t)stream_max_qg(h->d_pad);
-        const int64_t rows_pad =
-            small ? (B <= grp ? round_up(B, 16) : round_up(B, grp)) : round_up(B, kGemmQueryTile);
+        const bool wide = small && is_wide(B, h->d_pad);
+        const int64_t rows_pad = !small || wide ? round_up(B, 128) : B <= grp ? round_up(B, 16) : round_up(B, grp);
         // up to 32 queries (at most two rows per wave) and d_pad = 2048 the streaming kernel normalises its queries
         // itself, saving the staging launch; with more rows per wave its prologue would cost more than that launch
         // (64 queries on 10k x 384 keys: ~5.7 us of prologue against ~4 us of staging), so they are staged
@@ -316,11 +318,14 @@ static int lookup_chunk(lacache_t h, const char* queries, int B, const VerifyArg
             ++h->prof_used;
         }
         // with profiling on, the events take the stage-1 kernel's own start and end times (launch_timed)
-        hipError_t e = small ? launch_stage1_stream(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s,
-                                                    e0, e1, fused ? queries : nullptr, h->dtype, h->d,
-                                                    whole ? &v : nullptr, h->done)
-                             : launch_stage1_gemm(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s,
-                                                  e0, e1);
+        hipError_t e;
+        if (wide)
+            e = launch_stage1_wide(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s, e0, e1);
+        else if (small)
+            e = launch_stage1_stream(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s, e0, e1,
+                                     fused ? queries : nullptr, h->dtype, h->d, whole ? &v : nullptr, h->done);
+        else
+            e = launch_stage1_gemm(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s, e0, e1);
         if (e != hipSuccess) return LACACHE_EHIP;
         if (whole) return LACACHE_OK;
     }

@@ -118,6 +118,13 @@ hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B,
                                 const VerifyArgs* verify = nullptr, uint32_t* done = nullptr);
 int stream_fused_ncq(int d_pad);
 
+// The streaming pass for more queries than LDS holds, of 769 to 1024 columns (is_wide): B <= kWideQueries (rows of qt
+// zero-padded to that); otherwise as launch_stage1_stream with staged queries.
+constexpr int kWideQueries = 128;
+inline bool is_wide(int B, int d_pad) { return B > 64 && B <= kWideQueries && (d_pad == 896 || d_pad == 1024); }
+hipError_t launch_stage1_wide(const uint16_t* keys, const uint16_t* qt, int B, int n_rows, int d_pad, uint64_t* part,
+                              int num_cu, int* P_out, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+
 // Stage 1, compute-bound path (matrix-core GEMM with a fused row maximum): queries qt (tiled, rows zero-padded
 // to a multiple of kGemmQueryTile) against n_rows keys.  The key store must hold whole tiles of kGemmKeyTile
 // rows plus one spare tile past the last one (the kernel prefetches into it; its rows are never scored).  Its

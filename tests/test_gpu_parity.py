@@ -443,6 +443,34 @@ def test_small_call_in_one_launch_matches_the_gemm_path(lc, N, d, m):
     c.close()
 
 
+@pytest.mark.parametrize("d", [769, 896, 1000, 1024])
+@pytest.mark.parametrize("N", [1, 16, 33, 513, 8193, 70_001])
+def test_wide_streaming_matches_the_gemm_path(lc, N, d):
+    """65 to 128 queries of 769 to 1024 columns, which the streaming pass keeps in registers: bit-equal to the GEMM
+    path at store sizes around its 16-row groups, its stages and the number of workgroups, with duplicate
+    keys (the lowest row wins) and rows of all-negative scores (padding never wins)."""
+    import torch
+    g = torch.Generator().manual_seed(N + d)
+    keys = torch.randn((N, d), generator=g).to(torch.bfloat16).cuda()
+    keys[N - N // 2:] = keys[:N // 2].clone()
+    tok = torch.randint(50, (N, 4), generator=g, dtype=torch.int32).cuda()
+    c = lc.LaCache(N, d, 4, lc.BF16, 128, 0)
+    c.insert(keys, keys, tok)
+    for B in (65, 80, 127, 128):
+        rows = torch.randint(N, (B,), generator=g).cuda()
+        q = (keys[rows].float() + 0.5 * torch.randn((B, d), generator=g).cuda()).to(torch.bfloat16)
+        q[::3] = -keys[0]
+        res = []
+        for small in (0, 128):
+            c.set_small_batch(small)
+            res.append([t.clone() for t in c.lookup(q, q, tok[rows], 0.5, 0.5, 4)])
+        for a, b in zip(*res):
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32)), (B, a, b)
+        assert torch.all(res[0][0] < N - N // 2)
+    assert c.replay_fallbacks() == 0
+    c.close()
+
+
 def test_calls_enqueued_on_side_streams(lc):
     """Inserts and lookups of two independent caches enqueued on two side streams (default priority), with no
     host synchronisation between the calls: a lookup sees every insert enqueued before it on its stream, and
