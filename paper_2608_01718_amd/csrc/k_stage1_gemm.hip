@@ -9,7 +9,8 @@
 //
 // Tiling.  A workgroup is four waves, one per SIMD, each with the whole
 // register file of its SIMD (256 accumulators + 256 vector registers).  It
-// owns a tile of 128 queries and walks a contiguous range of 512-key tiles;
+// owns a tile of 128 queries and walks a contiguous range of 512-key tiles
+// (lower ones where a range holds few: KB 16-row blocks per wave);
 // wave w multiplies keys w*128 .. w*128+127 of each tile against all 128
 // queries, as 8 x 8 blocks of v_mfma_f32_16x16x32_bf16 (keys as the row
 // operand).  The store's tiled layout makes every 1 KiB chunk (16 rows x 32
@@ -37,6 +38,7 @@
 // count (zero padding, which must never win) occur only in the last tile of
 // the last range and are masked there.  At the end each workgroup writes one
 // packed candidate per query.
+#include <initializer_list>
 #include <type_traits>
 
 #include "common.hpp"
@@ -47,9 +49,9 @@ namespace lacache {
 namespace {
 
 constexpr int kWK = 4;                 // waves per workgroup, one 128-key slice each
-constexpr int kKB = 8;                 // 16-row key blocks per wave
+constexpr int kMaxKB = 8;              // most 16-row key blocks per wave (KB of the kernel)
+constexpr int kMinKB = 5;              // fewest
 constexpr int kQB = 8;                 // 16-query blocks per wave (all waves share them)
-constexpr int kTK = kWK * kKB * 16;    // keys per workgroup tile
 constexpr int kTQ = kQB * 16;          // queries per workgroup tile
 constexpr int kS = 2;                  // 32-column steps per LDS stage of the query tile
 constexpr int kR = 4;                  // LDS stage slots
@@ -62,7 +64,7 @@ constexpr int kSlot = kSC * 1024;      // bytes per stage slot
 constexpr int kRing = kR * kSlot;      // bytes of the ring
 constexpr int kBest = kWK * kQB * 64 * 8;  // running best of every lane and query block (after the ring)
 constexpr int kLds = kRing + kBest;
-static_assert(kTK == kGemmKeyTile && kTQ == kGemmQueryTile, "tile sizes the host pads to");
+static_assert(kWK * kMaxKB * 16 == kGemmKeyTile && kTQ == kGemmQueryTile, "tile sizes the host pads to");
 static_assert(kU % kS == 0 && kU % kNK == 0 && kSC % kWK == 0, "");
 static_assert((kRing & (kRing - 1)) == 0, "ring size is a power of two");
 
@@ -91,10 +93,12 @@ __device__ inline void lds_barrier() {
 // query groups x (8 / xq) key parts; XCD x serves the query tiles of group x % xq against key part x / xq,
 // so each key range is fetched into as few L2s as possible while the query tiles an XCD re-reads stay
 // resident there.  Requires n_qtiles % xq == 0 and n_ranges % (8 / xq) == 0.
+template <int kKB>
 __global__ __launch_bounds__(kWK * 64, 1) void k_stage1_gemm(const u32x4* __restrict__ keys,
                                                              const u32x4* __restrict__ qt, int kc, int n_rows,
                                                              int n_ktiles, int n_qtiles, int n_ranges, int xq, int B,
                                                              int P, uint64_t* __restrict__ part) {
+    constexpr int kTK = kWK * kKB * 16;  // keys per workgroup tile
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int lane = threadIdx.x & 63;
     const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -147,15 +151,17 @@ __global__ __launch_bounds__(kWK * 64, 1) void k_stage1_gemm(const u32x4* __rest
     };
 
     // ---- keys: chunk (block kb, step j of tile t of the range) at byte ((t * kTK / 16 + kb) * kc + j) * 1024
-    // from the wave's first block.  The loads run kPD steps ahead without bounds checks: the store keeps one
-    // spare tile of zero rows past its last tile, so the prefetches beyond a range stay inside it.
+    // from the wave's first block.  The loads run kPD steps ahead without bounds checks: the store holds whole tiles
+    // of 512 rows and one spare such tile of zero rows, so a tile and the prefetch beyond a range stay inside it.
+    // Lower tiles may end anywhere in a 512-row one: their prefetch starts the range's last tile over instead.
     const __amdgpu_buffer_rsrc_t krs = make_rsrc(keys + ((int64_t)kt0 * (kTK / 16) + wk * kKB) * kc * 64);
     int kstep = 0, ksoff = 0;  // step inside its tile of the next key load, its byte offset in the range
+    int wrap = 0;              // what takes that offset from the end of a tile to the next one to load
     auto key_next = [&]() {
         ksoff += 1024;
         if (++kstep == kc) {
             kstep = 0;
-            ksoff += (kTK / 16 - 1) * kc * 1024;
+            ksoff += kKB == kMaxKB ? (kTK / 16 - 1) * kc * 1024 : wrap;
         }
     };
     u32x4 kf[kNK][kKB];
@@ -217,7 +223,7 @@ __global__ __launch_bounds__(kWK * 64, 1) void k_stage1_gemm(const u32x4* __rest
             const bool zero = FIRST && u == 0;
             if (u % kS == kS - 1) {
                 key_load(kf[(u + kPD) % kNK]);
-                mm(0, kKB / 2, kf[u % kNK], qf[u & 1], zero);
+                mm(0, (kKB + 1) / 2, kf[u % kNK], qf[u & 1], zero);
                 spread_loads(std::integral_constant<int, kQB / 2>{});
                 __builtin_amdgcn_sched_barrier(0);
                 stage_store();
@@ -225,7 +231,7 @@ __global__ __launch_bounds__(kWK * 64, 1) void k_stage1_gemm(const u32x4* __rest
                 stage_load();
                 rd_base = (rd_base + kSlot) & (kRing - 1);
                 read_q(rd_base, 0, qf[(u + 1) & 1]);
-                mm(kKB / 2, kKB, kf[u % kNK], qf[u & 1], zero);
+                mm((kKB + 1) / 2, kKB, kf[u % kNK], qf[u & 1], zero);
             } else {
                 key_load(kf[(u + kPD) % kNK]);
                 read_q(rd_base, u % kS + 1, qf[(u + 1) & 1]);
@@ -237,6 +243,7 @@ __global__ __launch_bounds__(kWK * 64, 1) void k_stage1_gemm(const u32x4* __rest
     };
 
     for (int t = 0; t < T; ++t) {
+        if constexpr (kKB < kMaxKB) wrap = ((t + 1 < T ? kTK / 16 : 0) - 1) * kc * 1024;
         body(std::true_type{});
         for (int j = kU; j < kc; j += kU) body(std::false_type{});
         // epilogue of tile kt0 + t: lane holds rows 4 * (lane / 16) + i of block kb for query lane % 16 of
@@ -304,34 +311,70 @@ hipError_t launch_stage1_gemm(const uint16_t* keys, const uint16_t* qt, int B, i
     const int kc = d_pad / 32;
     if (n_rows <= 0 || B <= 0 || kc % kU != 0) return hipErrorInvalidValue;
     const int n_qtiles = (B + kTQ - 1) / kTQ;
-    const int n_ktiles = (n_rows + kTK - 1) / kTK;
-    // one workgroup per CU (each wave holds a SIMD's whole register file): as many key ranges per query tile
-    // as fill the CUs once
-    int n_ranges = (num_cu + n_qtiles - 1) / n_qtiles;
-    if (n_ranges > n_ktiles) n_ranges = n_ktiles;
-    if (n_ranges > kMaxPartials) n_ranges = kMaxPartials;
-    // the key offsets of a range stay below 2^31 bytes (its tiles plus the prefetch overrun)
-    const int64_t tile_bytes = (int64_t)kTK * d_pad * 2;
-    const int64_t max_tiles = ((int64_t(1) << 31) - 1) / tile_bytes - 1;
-    if (max_tiles < 1) return hipErrorInvalidValue;
-    if ((n_ktiles + n_ranges - 1) / n_ranges > max_tiles) n_ranges = (int)((n_ktiles + max_tiles - 1) / max_tiles);
-    if (n_ranges > kMaxPartials) return hipErrorInvalidValue;
-    *P_out = n_ranges;
     // XCD placement: the fewest query groups (1, 2, 4 or 8) whose query tiles fit one XCD's L2 beside the key
-    // stream, at most 3 MiB per XCD; plain round-robin when the counts do not divide evenly
-    int xq = 0;
-    for (int x = 1; x <= 8; x *= 2) {
-        if (n_qtiles % x != 0 || n_ranges % (8 / x) != 0) continue;
-        if ((int64_t)(n_qtiles / x) * kTQ * d_pad * 2 <= (int64_t(3) << 20)) {
-            xq = x;
-            break;
+    // stream, at most 3 MiB per XCD (a count of tiles that does not divide evenly: all in one group up to 4.5 MiB);
+    // plain round-robin (0) when the counts allow none
+    auto placement = [&](int ranges) {
+        for (int x = 1; x <= 8; x *= 2)
+            if (n_qtiles % x == 0 && ranges % (8 / x) == 0 &&
+                (int64_t)(n_qtiles / x) * kTQ * d_pad * 2 <= (int64_t(3) << 20))
+                return x;
+        return ranges % 8 == 0 && (int64_t)n_qtiles * kTQ * d_pad * 2 <= (int64_t(9) << 19) ? 1 : 0;
+    };
+    // Key ranges and tile height, by the time of the longest workgroup in key blocks.  A CU holds one workgroup (each
+    // wave has a SIMD's whole register file), so what counts is rounds of workgroups x tiles of a range x rows of a
+    // tile, and:
+    // - one workgroup more than the CUs costs a whole round: 2200 queries (18 query tiles) on 1M x 768 keys in 15
+    //   ranges took 4.97 ms, 2.69 ms in 14; several rounds are weighed too, they fill the last one better;
+    // - without a placement the workgroups of a range sit on several XCDs, each fetching its keys; with few query
+    //   tiles that is slower than the contraction.  300 queries (3 tiles) on 200k x 768 keys in 86 ranges (both
+    //   faults) took 200 us, 113 us in 80; 600 (5 tiles) on 500k x 768 818 and 427 us;
+    // - a range of few tiles wastes much of its last one, which a lower tile avoids (64 rows per block, 8 blocks at
+    //   most; half a block per tile for the loop, 7 % more per row of a lower tile, which feeds fewer products per
+    //   query fragment): 256 queries on 100k x 1024 keys, 782 rows per range, two tiles of 448 rows 60.6 us, of
+    //   512 64.3 us; on 50k x 384, one of 448 rows 16.3 us, of 512 20.7 us.
+    const int scattered = n_qtiles == 1 ? 100 : n_qtiles < 12 ? 160 : n_qtiles < 24 ? 112 : 103;  // percent
+    int kb = kMaxKB, n_ktiles = 0, n_ranges = 0, xq = 0;
+    int64_t least = INT64_MAX;
+    for (int x = kMaxKB; x >= kMinKB; --x) {
+        const int tiles = (n_rows + kWK * x * 16 - 1) / (kWK * x * 16);
+        for (int rounds = 1; rounds <= 3; ++rounds) {
+            const int fill = rounds * num_cu / n_qtiles, most = fill < 1 ? 1 : fill < tiles ? fill : tiles;
+            for (int mask : {0, 1, 3, 7}) {
+                const int ranges = most & ~mask;
+                if (ranges < 1) continue;
+                const int place = placement(ranges);
+                const int64_t turns = ((int64_t)ranges * n_qtiles + num_cu - 1) / num_cu;
+                const int64_t cost = turns * ((tiles + ranges - 1) / ranges) * (2 * x + 1) * (x == kMaxKB ? 100 : 107) *
+                                     (place > 0 ? 100 : scattered);
+                if (cost < least) kb = x, n_ktiles = tiles, n_ranges = ranges, xq = place, least = cost;
+            }
         }
     }
-    static std::atomic<uint64_t> lds_done{0};
-    hipError_t e = allow_dynamic_lds((const void*)k_stage1_gemm, kLds, lds_done);
-    if (e != hipSuccess) return e;
-    return launch_timed(k_stage1_gemm, dim3(n_qtiles * n_ranges), dim3(kWK * 64), kLds, s, e0, e1, (const u32x4*)keys,
-                        (const u32x4*)qt, kc, n_rows, n_ktiles, n_qtiles, n_ranges, xq, B, n_ranges, part);
+    if (n_ranges > kMaxPartials) n_ranges = kMaxPartials, xq = placement(n_ranges);
+    // the key offsets of a range stay below 2^31 bytes (its tiles plus the prefetch overrun)
+    const int64_t tile_bytes = (int64_t)kWK * kb * 16 * d_pad * 2;
+    const int64_t max_tiles = ((int64_t(1) << 31) - 1) / tile_bytes - 1;
+    if (max_tiles < 1) return hipErrorInvalidValue;
+    if ((n_ktiles + n_ranges - 1) / n_ranges > max_tiles) {
+        n_ranges = (int)((n_ktiles + max_tiles - 1) / max_tiles);
+        xq = placement(n_ranges);
+    }
+    if (n_ranges > kMaxPartials) return hipErrorInvalidValue;
+    *P_out = n_ranges;
+    auto run = [&](auto kernel, std::atomic<uint64_t>& lds_done) {
+        const hipError_t e = allow_dynamic_lds((const void*)kernel, kLds, lds_done);
+        if (e != hipSuccess) return e;
+        return launch_timed(kernel, dim3(n_qtiles * n_ranges), dim3(kWK * 64), kLds, s, e0, e1, (const u32x4*)keys,
+                            (const u32x4*)qt, kc, n_rows, n_ktiles, n_qtiles, n_ranges, xq, B, n_ranges, part);
+    };
+    static std::atomic<uint64_t> lds_done[kMaxKB + 1] = {};
+    switch (kb) {
+        case 5: return run(k_stage1_gemm<5>, lds_done[5]);
+        case 6: return run(k_stage1_gemm<6>, lds_done[6]);
+        case 7: return run(k_stage1_gemm<7>, lds_done[7]);
+        default: return run(k_stage1_gemm<8>, lds_done[8]);
+    }
 }
 
 }  // namespace lacache

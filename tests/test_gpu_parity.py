@@ -471,6 +471,34 @@ def test_wide_streaming_matches_the_gemm_path(lc, N, d):
     c.close()
 
 
+@pytest.mark.parametrize("N,d", [(1, 64), (449, 128), (5000, 320), (27_777, 256), (60_000, 100), (100_003, 64)])
+def test_gemm_launch_shapes_match_the_streaming_path(lc, N, d):
+    """Key tiles of every height and key ranges of every placement (odd and even numbers of 128-query tiles, fewer
+    and more of them than the workgroups of one round), in a store with no room to spare: bit-equal to the
+    streaming path, which takes the same queries 64 at a time; with duplicate keys the lowest row wins."""
+    import torch
+    g = torch.Generator().manual_seed(N)
+    keys = torch.randn((N, d), generator=g).to(torch.bfloat16).cuda()
+    keys[N - N // 3:] = keys[:N // 3].clone()
+    tok = torch.randint(50, (N, 4), generator=g, dtype=torch.int32).cuda()
+    c = lc.LaCache(N, d, 4, lc.BF16, 65_536, 0)
+    c.insert(keys, keys, tok)
+    for B in (1, 129, 300, 640, 1100, 2200, 3300, 40_000 if N <= 5000 else 4096):
+        rows = torch.randint(N, (B,), generator=g).cuda()
+        q = (keys[rows].float() + 0.5 * torch.randn((B, d), generator=g).cuda()).to(torch.bfloat16)
+        q[::5] = -keys[0]
+        u = tok[rows].contiguous()
+        c.set_small_batch(0)
+        whole = c.lookup(q, q, u, 0.5, 0.5, 4)
+        c.set_small_batch(64)
+        parts = [c.lookup(q[i:i + 64], q[i:i + 64], u[i:i + 64], 0.5, 0.5, 4) for i in range(0, B, 64)]
+        for a, b in zip(whole, (torch.cat(x) for x in zip(*parts))):
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32)), B
+        assert torch.all(whole[0] < N - N // 3)
+    assert c.replay_fallbacks() == 0
+    c.close()
+
+
 def test_calls_enqueued_on_side_streams(lc):
     """Inserts and lookups of two independent caches enqueued on two side streams (default priority), with no
     host synchronisation between the calls: a lookup sees every insert enqueued before it on its stream, and
