@@ -566,7 +566,7 @@ __global__ __launch_bounds__(256) void k_lsh_verify(const u32x4* __restrict__ ke
         best = umax64(best, pack_top1(acc, i));
     }
     if (lane == 0) n_cand[b] = (int32_t)c_all;
-    verify_query(b, best, unpack_idx(best), unpack_score(best), n_rows, dtype, v, lane);
+    verify_query<IN_PLACE>(b, best, unpack_idx(best), unpack_score(best), n_rows, dtype, v, lane);
 }
 
 hipError_t launch_tile_hyperplanes(const uint16_t* src, int bits, int d, int d_pad, uint16_t* dst, hipStream_t s) {

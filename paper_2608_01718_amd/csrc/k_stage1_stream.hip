@@ -191,7 +191,7 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
                 m = umax64(m, __hip_atomic_load(&part[(int64_t)b * n_ranges + p], __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT));
             m = wave_max_u64(m);
-            verify_query(b, m, unpack_idx(m), unpack_score(m), n_rows, dtype, v, lane);
+            verify_query<IN_PLACE>(b, m, unpack_idx(m), unpack_score(m), n_rows, dtype, v, lane);
         }
     }
 }

@@ -105,10 +105,33 @@ __device__ inline int32_t replay_group16(const u32x4* __restrict__ keys, const u
     return replay_pick_row(p, fallback);
 }
 
+// Whether the packed stage-1 result m (0: no candidate) is a stage-1 hit.
+__device__ inline bool stage1_hit(uint64_t m, float tau_q) {
+    return m != 0ull && fminf(fmaxf(unpack_score(m), -1.0f), 1.0f) >= tau_q;
+}
+
+// What stage 2 reads of the query: lane l's part of the lookahead row under one model (d_pad <= 1024; wider rows are
+// read where they are used) and, in u0, lookahead token l.  A hit's are loaded before its entry is known
+// exactly, so that they are on their way while the group replay waits for its own.
+struct Lookahead {
+    RawRow<2> row;
+    int32_t u0;
+};
+__device__ __forceinline__ const char* lookahead_row(const PrefixModels& M, int mi, int b, int dtype) {
+    return (const char*)M.la[mi] + (int64_t)b * M.d[mi] * (dtype == 0 ? 4 : 2);
+}
+__device__ __forceinline__ void load_lookahead(const VerifyArgs& v, int b, int dtype, bool hit, int lane, Lookahead& x) {
+    row_load<2>(lookahead_row(v.models, 0, b, dtype), dtype, v.models.d[0], hit && v.models.d_pad[0] <= 1024, lane, x.row);
+    x.u0 = hit && lane < v.k ? v.la_tok[(int64_t)b * v.k + lane] : 0;
+}
+
 // One wave: outputs of query b for the packed stage-1 result m (0: no candidate) naming entry i with raw
-// score s_raw.
+// score s_raw.  PRELOADED: la as load_lookahead gives it (else it is loaded here); AHEAD: with several prefix models
+// the next one's rows are loaded while this one's are multiplied (for kernels that have the registers).
+enum VerifyLoads { IN_PLACE, PRELOADED, AHEAD };
+template <VerifyLoads MODE>
 __device__ inline void verify_query(int b, uint64_t m, int32_t i, float s_raw, int n_rows, int dtype,
-                                    const VerifyArgs& v, int lane) {
+                                    const VerifyArgs& v, int lane, Lookahead la = {}) {
     const PrefixModels& M = v.models;
     const int32_t* __restrict__ la_tok = v.la_tok;
     const int32_t* __restrict__ tokens = v.tokens;
@@ -135,39 +158,55 @@ __device__ inline void verify_query(int b, uint64_t m, int32_t i, float s_raw, i
     const int32_t* ut = la_tok + (int64_t)b * k;
     const int32_t* tt = tokens + (int64_t)i * k_cap;
     const bool has0 = lane < k;
-    const int32_t u0 = has0 ? ut[lane] : 0, t0 = has0 ? tt[lane] : 0;
+    if constexpr (MODE == IN_PLACE) la.u0 = has0 ? ut[lane] : 0;
+    const int32_t t0 = has0 ? tt[lane] : 0;
 
     // for every prefix model: normalise the lookahead embedding exactly as stored vectors are and dot it with
     // the entry's stored prefix row; the embedding check passes only if every model reaches its threshold
     // (Section 4.4: with m lookahead checks a hit needs all of them)
-    const size_t esz = dtype == 0 ? 4 : 2;
     bool all_pass = true;
+    u32x4 e[2], e_next[2];
+    auto load_entry = [&](int mi, u32x4 (&x)[2]) {  // lane's part of the entry's prefix row (d_pad <= 1024)
+        const u32x4* er = (const u32x4*)(M.emb[mi] + (int64_t)i * M.d_pad[mi]);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int j0 = lane * 8 + 512 * c;
+            x[c] = j0 < M.d_pad[mi] && M.d_pad[mi] <= 1024 ? er[j0 >> 3] : u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+    if constexpr (MODE != IN_PLACE) load_entry(0, e);
     for (int mi = 0; mi < M.m; ++mi) {
         const int d = M.d[mi], d_pad = M.d_pad[mi];
-        const char* src = (const char*)M.la[mi] + (int64_t)b * d * esz;
-        const u32x4* er = (const u32x4*)(M.emb[mi] + (int64_t)i * d_pad);
+        const char* src = lookahead_row(M, mi, b, dtype);
+        RawRow<2> next;
+        if (MODE == IN_PLACE || (MODE == PRELOADED && mi > 0)) {
+            load_entry(mi, e);
+            row_load<2>(src, dtype, d, d_pad <= 1024, lane, la.row);
+        }
+        if (MODE == AHEAD && mi + 1 < M.m) {
+            row_load<2>(lookahead_row(M, mi + 1, b, dtype), dtype, M.d[mi + 1], M.d_pad[mi + 1] <= 1024, lane, next);
+            load_entry(mi + 1, e_next);
+        }
         float acc = 0.0f;
         // padded columns are zero on both sides
         if (d_pad <= 1024) {
-            // both rows loaded at once, the lookahead row kept in registers: the same norm, rounding and
-            // dot order as normalise_row, one wait for memory instead of three
+            // the lookahead row kept in registers: the same norm, rounding and dot order as normalise_row
             float x[2][8];
-            u32x4 e[2];
             uint32_t z[8];
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const int j0 = lane * 8 + 512 * c;
-                e[c] = j0 < d_pad ? er[j0 >> 3] : u32x4{0u, 0u, 0u, 0u};
-            }
-            row_to_regs<2>(src, dtype, d, true, lane, x);
+            row_unpack<2>(src, dtype, d, true, lane, la.row, x);
             const double n = regs_norm<2>(x);
             quantise_row<2>(x, n, quotient_rcp_f32(n), d, lane, z);
 #pragma unroll
             for (int c = 0; c < 2; ++c)
                 if (lane * 8 + 512 * c < d_pad) acc = dot8_bf16(piece(z, c), e[c], acc);
         } else {
+            const u32x4* er = (const u32x4*)(M.emb[mi] + (int64_t)i * d_pad);
             normalise_row(src, dtype, d, d_pad, true, lane,
                           [&](int j0, u32x4 w) { acc = dot8_bf16(w, er[j0 >> 3], acc); });
+        }
+        if (MODE == AHEAD && mi + 1 < M.m) {
+            la.row = next;
+            e[0] = e_next[0], e[1] = e_next[1];
         }
         acc = wave_sum_f32(acc);
         const float r = fminf(fmaxf(acc, -1.0f), 1.0f);
@@ -176,7 +215,7 @@ __device__ inline void verify_query(int b, uint64_t m, int32_t i, float s_raw, i
     }
 
     // first k tokens: lane j compares token j, 64 at a time
-    bool tok_eq = __ballot(has0 && u0 != t0) == 0ull;
+    bool tok_eq = __ballot(has0 && la.u0 != t0) == 0ull;
     for (int j0 = kWave; j0 < k; j0 += kWave) {
         const int j = j0 + lane;
         const bool differ = (j < k) && (ut[j] != tt[j]);
