@@ -119,3 +119,32 @@ def test_accept_full_size(lc):
     acc, pt, o, exact = _run(lc, lg, synth.BF16, tok, pd)
     say(f"[ok] exact lengths {exact}/{B}, mean accepted {acc.mean():.2f} of {k}")
     assert exact >= B - 2
+
+
+@pytest.mark.parametrize("f32", [True, False])
+def test_acceptance_row_alignment_and_counts(lc, f32):
+    """Rows that start anywhere in a 16-byte chunk (every remainder of the vocabulary size), rows shorter than a chunk,
+    and row counts on both sides of the limits between workgroup sizes, in buffers that start off a boundary:
+    against the float64 softmax.  A float32 sum of exponentials good to a few units in the last place is within
+    2e-5 (measured 1e-6)."""
+    import torch
+    g = torch.Generator("cuda").manual_seed(3)
+    dt = torch.float32 if f32 else torch.bfloat16
+    shapes = [(B, 1, V) for B in (1, 3) for V in (1, 2, 5, 7, 8, 9, 15, 16, 17, 2047, 8195, 8199)]
+    shapes += [(256, 1, 33), (257, 1, 33), (16, 64, 49_153), (41, 25, 49_153), (5, 3, 100_003)]
+    for B, k, V in shapes:
+        for shift in (0, 1, 3):
+            buf = torch.randn(B * k * V + 4, generator=g, device="cuda").mul_(3).to(dt)
+            x = buf[shift:shift + B * k * V].view(B, k, V)
+            if V > 4:
+                x[:, :, 1::3] = -float("inf")
+            tok = torch.randint(-1, V + 1, (B, k), generator=g, device="cuda", dtype=torch.int32)
+            pd = torch.rand((B, k), generator=g, device="cuda") / V
+            n, p = lc.lacache_accept_length(x, tok, pd)
+            inside = (tok >= 0) & (tok < V)
+            want = torch.softmax(x.double(), 2).gather(2, tok.clamp(0, V - 1).long()[..., None])[..., 0]
+            want = torch.where(inside, want, torch.zeros_like(want))
+            err = ((p.double() - want).abs() / want.clamp(min=1e-30))[want > 0]
+            assert err.numel() == 0 or err.max() <= 2e-5, (B, k, V, shift, err.max())
+            assert torch.all(p[want == 0] == 0)
+            assert torch.equal(n, (p >= pd).int().cumprod(1).sum(1).int())
