@@ -264,7 +264,8 @@ int lacache_accept_length(const void *logits, lacache_dtype dtype, int32_t V, co
  * multiple of 32 in 32 .. 256, max_candidates 1 .. 65536 entries kept per
  * query.  Allocates the index (signatures [capacity][bits / 32] and per-query
  * candidate lists), waits for `stream`, and computes the signatures of every
- * stored entry; later inserts add theirs.  Calling it again replaces the index.
+ * stored entry; later inserts add theirs.  Calling it again replaces the index
+ * (in the same buffers if bits and max_candidates are the same).
  */
 int lacache_enable_lsh(lacache_t h, int32_t bits, const uint16_t *hyperplanes, int32_t max_candidates, void *stream);
 

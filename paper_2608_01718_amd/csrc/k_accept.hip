@@ -83,7 +83,8 @@ __global__ __launch_bounds__(kThreads) void k_token_prob(const void* __restrict_
     for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
         const char* r = (const char*)logits + row * (int64_t)V * esz;
         float m = -__builtin_inff(), s = 0.0f;
-        int head = (int)((0 - (uintptr_t)r & 15) / esz);  // elements before the first whole chunk
+        // elements before the first whole chunk (all of them if no element starts on the boundary)
+        int head = (uintptr_t)r % esz == 0 ? (int)(((0 - (uintptr_t)r) & 15) / esz) : V;
         if (head > V) head = V;
         const char* rc = r + head * esz;
         const int nchunks = (V - head) / 8;
@@ -100,11 +101,11 @@ __global__ __launch_bounds__(kThreads) void k_token_prob(const void* __restrict_
             load_chunk(rc + (size_t)c * 8 * esz, dtype, x);
             lse_add8(m, s, x);
         }
-        // the elements before and after the chunks, at most 7 of each: one per thread
+        // the elements before and after the chunks, one by one
         const int rest = V - nchunks * 8;
-        if (tid < rest) {
+        for (int v = tid; v < rest; v += kThreads) {
             float x[8];
-            x[0] = load_one(r, dtype, tid < head ? tid : nchunks * 8 + tid);
+            x[0] = load_one(r, dtype, v < head ? v : nchunks * 8 + v);
 #pragma unroll
             for (int e = 1; e < 8; ++e) x[e] = -__builtin_inff();
             lse_add8(m, s, x);

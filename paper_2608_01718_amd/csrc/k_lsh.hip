@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256, HB <= 6 ? 2 : 1) void k_simhash_bulk(const u32
     const uint32_t lane16 = (uint32_t)lane * 16;
 
     // rows: chunk (block kb, step j) of the wave's part of a tile at byte (kb * kc + j) * 1024 from the tile's
-    // base.  A tile reads at most 511 rows past the call's last one, fewer than the store's 512 spare rows.  The
+    // base.  A tile reads at most 255 rows past the call's last one, fewer than the store's 512 spare rows.  The
     // loads run SETS - 1 steps ahead into the next tile; in the last tile they start over, and are not used.
     const char* kbase = (const char*)(rows_tiled + (g0 + (int64_t)t0 * kTile + wv * kRB) * kc * 64);
     const int tile_bytes = kTile * kc * 1024;
