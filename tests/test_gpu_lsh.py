@@ -273,6 +273,65 @@ def test_candidate_scan_at_block_edges(lc, bits):
         cq.close()
 
 
+@pytest.mark.parametrize("bits,B", [(64, 4), (96, 17), (256, 100), (256, 481)])
+def test_wide_radius_lists_every_candidate(lc, bits, B):
+    """Radii that make half or all of the entries candidates: the counts are exact, the list holds every one of them
+    (the winner is the best candidate by the float32 scores), and a list too short for them keeps candidates only."""
+    import torch
+    d, N, g = 64, 20011, torch.Generator().manual_seed(bits + B)
+    keys = torch.randn((N, d), generator=g).to(torch.bfloat16).cuda()
+    q = torch.randn((B, d), generator=g).to(torch.bfloat16).cuda()
+    hp = torch.randn((bits, d), generator=g).to(torch.bfloat16).cuda()
+    tok = torch.zeros((N, 1), dtype=torch.int32, device="cuda")
+    c, cq = (lc.LaCache(n, d, 1, lc.BF16, 512, 0) for n in (N, B))
+    for x, rows in ((c, keys), (cq, q)):
+        x.insert(rows, rows, tok[:rows.shape[0]])
+        x.enable_lsh(bits, hp, 32768)
+    unpack = lambda x: ((x.view(torch.uint8)[..., None] >> torch.arange(8, device="cuda", dtype=torch.uint8)) & 1).flatten(1)  # noqa: E731
+    kb, qb = unpack(c.export_signatures(0, N)).float(), unpack(cq.export_signatures(0, B)).float()
+    dist = (qb.sum(1)[:, None] + kb.sum(1)[None] - 2 * qb @ kb.T).round().int()
+    z, zq = (x.export(0, n)[0].view(torch.bfloat16).float() for x, n in ((c, N), (cq, B)))
+    scores = zq @ z.T
+    at = torch.arange(B, device="cuda")
+    for max_cand in (32768, 5):
+        c.enable_lsh(bits, hp, max_cand)
+        for radius in (bits // 2, bits):
+            idx, score, _, _, n_cand = c.lookup_lsh(q, q, tok[:B], -1.0, 2.0, 1, radius)
+            cand = dist <= radius
+            assert torch.equal(n_cand.long(), cand.sum(1))
+            assert torch.all(cand[at, idx.long()])
+            if max_cand > N:
+                best = torch.where(cand, scores, -2.0).max(1).values.clamp(-1, 1)
+                assert torch.all((score - best).abs() <= 1e-5)
+    c.close()
+    cq.close()
+
+
+def test_wide_radius_scan_time(lc):
+    """Counting many candidates costs little beside finding them: 16 queries with every one of 300,000 entries a
+    candidate (one kept).  An addition to the query's count per candidate takes 11 ms, one per 64 entries 0.07 ms."""
+    import torch
+    N, d, bits, B = 300_000, 64, 64, 16
+    keys = torch.randn((N, d), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16).cuda()
+    tok = torch.zeros((N, 1), dtype=torch.int32, device="cuda")
+    c = lc.LaCache(N, d, 1, lc.BF16, 64, 0)
+    c.insert(keys, keys, tok)
+    c.enable_lsh(bits, to_dev(synth.hyperplanes(bits, d, seed=9)), 1)
+    call = lambda: c.lookup_lsh(keys[:B], keys[:B], tok[:B], 0.9, 0.85, 1, bits)  # noqa: E731
+    for _ in range(3):
+        assert torch.all(call()[4] == N)
+    e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+    e0.record()
+    for _ in range(5):
+        call()
+    e1.record()
+    torch.cuda.synchronize()
+    ms = e0.elapsed_time(e1) / 5
+    say(f"[ok] {B} queries x {N} candidates: {ms:.3f} ms")
+    assert ms < 3.0
+    c.close()
+
+
 def test_lsh_recall_full_size_serve(lc):
     """The serving workload at full size (1M x 768, 4096 queries): 256-bit signatures, radius 64.  Against
     the exact lookup every stage-1 hit is found (same entry, same decision) and the candidate lists stay
