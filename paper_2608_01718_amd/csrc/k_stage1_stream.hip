@@ -74,7 +74,7 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
         // fit in 32 registers all of the wave's rows are loaded before any is reduced, so their loads overlap.
         const size_t esz = dtype == 0 ? 4 : 2;
         constexpr int kAhead = QG * NCQ <= 4 ? QG : 1;      // rows held in registers at once
-#pragma unroll
+#pragma unroll 1
         for (int q0 = 0; q0 < QG; q0 += kAhead) {
             float x[kAhead][NCQ][8];
 #pragma unroll
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
         else
             part[(int64_t)q * n_ranges + r] = m;
     }
-    if constexpr (NCQ > 0) {
+    if constexpr (stream_ends_lookup(NCQ)) {
         // Small calls: the workgroup that ends last merges the partials and runs stage 2, a wave per query, which
         // saves the launch that would follow (one query on 10k x 384 float32 keys, back to back: 12.7 -> 10.1 us
         // a call).  More than two queries per wave would take longer one after another than that launch.
@@ -336,7 +336,7 @@ hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B,
                                 const void* qraw, int dtype, int d, const VerifyArgs* verify, uint32_t* done) {
     const int kc = d_pad / 32;
     const int ncq = qraw == nullptr ? 0 : stream_fused_ncq(d_pad);
-    if (verify != nullptr && (qraw == nullptr || done == nullptr)) return hipErrorInvalidValue;
+    if (verify != nullptr && (!stream_ends_lookup(ncq) || done == nullptr)) return hipErrorInvalidValue;
     if (qraw != nullptr && (ncq == 0 || B > 32 || d < 1 || d > d_pad || (dtype != 0 && dtype != 1)))
         return hipErrorInvalidValue;
     const int groups = (n_rows + 15) / 16;

@@ -306,7 +306,7 @@ static int lookup_chunk(lacache_t h, const char* queries, int B, const VerifyArg
         const bool fused = small && B <= 32 && stream_fused_ncq(h->d_pad) > 0;
         // its last workgroup also ends the lookup (one launch per call) while its 16 waves, a query each, have at
         // most two embedding checks to run one after another
-        const bool whole = fused && (B <= 16 || v.models.m == 1);
+        const bool whole = fused && stream_ends_lookup(stream_fused_ncq(h->d_pad)) && (B <= 16 || v.models.m == 1);
         if (!fused && launch_normalise(queries, h->dtype, B, rows_pad, h->d, h->d_pad, h->qt, 0, true, s) != hipSuccess)
             return LACACHE_EHIP;
         hipEvent_t e0 = nullptr, e1 = nullptr;

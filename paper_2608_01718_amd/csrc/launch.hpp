@@ -108,15 +108,19 @@ struct VerifyArgs {
 // part[b * P + p] (P <= kMaxPartials).  Returns the number of partials P through *P_out.
 // With events e0 / e1 the kernel's run time is recorded into them (launch_timed).  With qraw (the caller's
 // [B][d] query rows, dtype 0 f32 / 1 bf16) the kernel normalises the queries itself and qt is not read; this
-// takes d_pad <= 2048 (stream_fused_ncq(d_pad) > 0) and B <= 32.  With `verify` too (B <= 32) the workgroup that
-// ends last also merges the partials and runs stage 2, so no launch follows; done: kDoneWords words, zero
-// between launches (the kernel leaves them so).
+// takes d_pad <= 2048 (stream_fused_ncq(d_pad) > 0) and B <= 32.  With `verify` too (B <= 32 and
+// stream_ends_lookup) the workgroup that ends last also merges the partials and runs stage 2, so no launch follows;
+// done: kDoneWords words, zero between launches (the kernel leaves them so).
 constexpr int kDoneWords = 9 * 32;
 hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B, int n_rows, int d_pad,
                                 uint64_t* part, int num_cu, int* P_out, hipStream_t s, hipEvent_t e0 = nullptr,
                                 hipEvent_t e1 = nullptr, const void* qraw = nullptr, int dtype = 0, int d = 0,
                                 const VerifyArgs* verify = nullptr, uint32_t* done = nullptr);
 int stream_fused_ncq(int d_pad);
+// Whether the kernel that normalises queries of up to 512 ncq columns has stage 2 in it too.  Not the widest: the two
+// together need more registers than a wave of its 16 has (176 bytes of scratch a lane: 16 and 32 queries on 200k x
+// 1536 float32 keys 125 and 133 us, 110 and 115 us with the launch that follows).
+constexpr bool stream_ends_lookup(int ncq) { return ncq == 1 || ncq == 2; }
 
 // The streaming pass for more queries than LDS holds, of 769 to 1024 columns (is_wide): B <= kWideQueries (rows of qt
 // zero-padded to that); otherwise as launch_stage1_stream with staged queries.
