@@ -164,10 +164,10 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
         else
             part[(int64_t)q * n_ranges + r] = m;
     }
-    if constexpr (stream_ends_lookup(NCQ)) {
+    if constexpr (stream_ends_lookup(QG, NCQ)) {
         // Small calls: the workgroup that ends last merges the partials and runs stage 2, a wave per query, which
         // saves the launch that would follow (one query on 10k x 384 float32 keys, back to back: 12.7 -> 10.1 us
-        // a call).  More than two queries per wave would take longer one after another than that launch.
+        // a call; lookup_in_one_launch says for which calls).
         if (done == nullptr) return;
         last_workgroup_wait();
         __syncthreads();
@@ -185,7 +185,8 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
         }
         __syncthreads();
         if (*last == 0u) return;
-        for (int b = wid; b < B; b += kStreamWaves) {
+        if (wid < B) {
+            const int b = wid;
             uint64_t m = 0;
             for (int p = lane; p < n_ranges; p += kWave)
                 m = umax64(m, __hip_atomic_load(&part[(int64_t)b * n_ranges + p], __ATOMIC_RELAXED,
@@ -336,7 +337,7 @@ hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B,
                                 const void* qraw, int dtype, int d, const VerifyArgs* verify, uint32_t* done) {
     const int kc = d_pad / 32;
     const int ncq = qraw == nullptr ? 0 : stream_fused_ncq(d_pad);
-    if (verify != nullptr && (!stream_ends_lookup(ncq) || done == nullptr)) return hipErrorInvalidValue;
+    if (verify != nullptr && (B > 16 || !stream_ends_lookup(1, ncq) || done == nullptr)) return hipErrorInvalidValue;
     if (qraw != nullptr && (ncq == 0 || B > 32 || d < 1 || d > d_pad || (dtype != 0 && dtype != 1)))
         return hipErrorInvalidValue;
     const int groups = (n_rows + 15) / 16;

@@ -304,9 +304,9 @@ static int lookup_chunk(lacache_t h, const char* queries, int B, const VerifyArg
         // itself, saving the staging launch; with more rows per wave its prologue would cost more than that launch
         // (64 queries on 10k x 384 keys: ~5.7 us of prologue against ~4 us of staging), so they are staged
         const bool fused = small && B <= 32 && stream_fused_ncq(h->d_pad) > 0;
-        // its last workgroup also ends the lookup (one launch per call) while its 16 waves, a query each, have at
-        // most two embedding checks to run one after another
-        const bool whole = fused && stream_ends_lookup(stream_fused_ncq(h->d_pad)) && (B <= 16 || v.models.m == 1);
+        int64_t resp_columns = 0;
+        for (int i = 0; i < v.models.m; ++i) resp_columns += v.models.d_pad[i];
+        const bool whole = fused && lookup_in_one_launch(B, n_rows, h->d_pad, resp_columns);
         if (!fused && launch_normalise(queries, h->dtype, B, rows_pad, h->d, h->d_pad, h->qt, 0, true, s) != hipSuccess)
             return LACACHE_EHIP;
         hipEvent_t e0 = nullptr, e1 = nullptr;

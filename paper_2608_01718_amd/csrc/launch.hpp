@@ -108,8 +108,8 @@ struct VerifyArgs {
 // part[b * P + p] (P <= kMaxPartials).  Returns the number of partials P through *P_out.
 // With events e0 / e1 the kernel's run time is recorded into them (launch_timed).  With qraw (the caller's
 // [B][d] query rows, dtype 0 f32 / 1 bf16) the kernel normalises the queries itself and qt is not read; this
-// takes d_pad <= 2048 (stream_fused_ncq(d_pad) > 0) and B <= 32.  With `verify` too (B <= 32 and
-// stream_ends_lookup) the workgroup that ends last also merges the partials and runs stage 2, so no launch follows;
+// takes d_pad <= 2048 (stream_fused_ncq(d_pad) > 0) and B <= 32.  With `verify` too (lookup_in_one_launch) the
+// workgroup that ends last also merges the partials and runs stage 2, so no launch follows;
 // done: kDoneWords words, zero between launches (the kernel leaves them so).
 constexpr int kDoneWords = 9 * 32;
 hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B, int n_rows, int d_pad,
@@ -117,10 +117,23 @@ hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B,
                                 hipEvent_t e1 = nullptr, const void* qraw = nullptr, int dtype = 0, int d = 0,
                                 const VerifyArgs* verify = nullptr, uint32_t* done = nullptr);
 int stream_fused_ncq(int d_pad);
-// Whether the kernel that normalises queries of up to 512 ncq columns has stage 2 in it too.  Not the widest: the two
-// together need more registers than a wave of its 16 has (176 bytes of scratch a lane: 16 and 32 queries on 200k x
-// 1536 float32 keys 125 and 133 us, 110 and 115 us with the launch that follows).
-constexpr bool stream_ends_lookup(int ncq) { return ncq == 1 || ncq == 2; }
+// Whether a lookup of B queries (d_pad columns) on n_rows entries, its prefix models of resp_columns padded columns in
+// all, ends in its streaming launch.  That saves a launch, but one workgroup then does what the launch spreads over
+// the chip, each wave a query, one model after another.  One launch / two, us a call, back to back: 1, 8, 16 and 32
+// queries on 10k x 384 float32 keys 9.6 / 10.8, 10.5 / 11.5, 11.8 / 12.3, 16.6 / 14.5; on 200k x 768 bfloat16 keys
+// 53.6 / 53.9, 52.6 / 53.1, 54.3 / 54.1, 60.2 / 56.3; 20k x 768 float32 entries with four models (3200 columns), 1, 8
+// and 16 queries 17.1 / 17.7, 19.6 / 19.9, 24.4 / 21.1; bfloat16 ones with two of 1536 and 2048 columns 20.9 / 21.2,
+// 23.2 / 22.4, 27.8 / 23.1.  In a replayed graph, where a launch costs less, the two are even up to 4 queries, 8 take
+// up to 0.4 us longer in one launch and 16 0.6 to 1.8 us; so 9 to 16 queries take one launch only on the smallest
+// stores, where calls wait for the host (16 queries on 10k x 64 bfloat16 keys 9.2 / 10.1 us, on 10k x 384 11.3 / 11.7,
+// on 200k x 64 14.7 / 14.6).  Wider keys leave no registers for stage 2 beside the normaliser (176 bytes of scratch a
+// lane: 16 queries on 200k x 1536 float32 keys 125 us, 110 us in two launches).
+inline bool lookup_in_one_launch(int B, int64_t n_rows, int d_pad, int64_t resp_columns) {
+    const int most = n_rows * d_pad <= (int64_t(1) << 23) ? 16 : 8;
+    return B <= most && d_pad <= 1024 && B * resp_columns <= 12288;
+}
+// The kernels (16 qg queries, normalised in up to 512 ncq columns) that have stage 2 in them for it.
+constexpr bool stream_ends_lookup(int qg, int ncq) { return qg == 1 && (ncq == 1 || ncq == 2); }
 
 // The streaming pass for more queries than LDS holds, of 769 to 1024 columns (is_wide): B <= kWideQueries (rows of qt
 // zero-padded to that); otherwise as launch_stage1_stream with staged queries.

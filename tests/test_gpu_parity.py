@@ -416,9 +416,9 @@ def test_determinism_and_paths_agree(lc, B):
 @pytest.mark.parametrize("m", [1, 3])
 @pytest.mark.parametrize("N,d", [(1, 64), (255, 384), (257, 768), (2100, 1500), (70_000, 384), (300_001, 128)])
 def test_small_call_in_one_launch_matches_the_gemm_path(lc, N, d, m):
-    """Calls whose last workgroup also ends the lookup (up to 32 queries, 16 with several prefix models; one, two
-    and fewer or more than eight workgroups): bit-equal to the GEMM path and its own finalize launch, on
-    repeated calls and on batch sizes around the limits."""
+    """Calls whose last workgroup also ends the lookup (up to 8 queries of up to 1024 columns, 16 on small
+    stores; one, two and fewer or more than eight workgroups): bit-equal to the GEMM path and its own finalize launch, on
+    repeated calls and on batch sizes around the limits of this and of normalising the queries in the kernel."""
     import torch
     g = torch.Generator().manual_seed(N + d + m)
     keys = torch.randn((N, d), generator=g).to(torch.bfloat16).cuda()
@@ -427,7 +427,7 @@ def test_small_call_in_one_launch_matches_the_gemm_path(lc, N, d, m):
     embs = [torch.randn((N, x), generator=g).to(torch.bfloat16).cuda() for x in dims]
     c = lc.LaCache(N, d, 9, lc.BF16, 64, 0, d_resp=dims)
     c.insert_ensemble(keys, embs, tok)
-    for B in (1, 15, 16, 17, 31, 32, 33):
+    for B in (1, 7, 8, 9, 15, 16, 17, 31, 32, 33):
         rows = torch.randint(N, (B,), generator=g).cuda()
         q = (keys[rows].float() + 0.3 * torch.randn((B, d), generator=g).cuda()).to(torch.bfloat16)
         las = [torch.where(torch.rand((B, 1), generator=g).cuda() < 0.5, e[rows], e[0]) for e in embs]

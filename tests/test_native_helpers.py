@@ -48,3 +48,22 @@ def test_replay_row_selection(replay_pick_checker):
     r = subprocess.run([replay_pick_checker], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
     assert r.stdout.startswith("ok ")
+
+
+@pytest.fixture(scope="module")
+def rules_checker(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("native") / "dispatch_rules")
+    subprocess.run([HIPCC, "-O2", "-std=c++17", "--offload-arch=gfx950",
+                    "-I", os.path.join(ROOT, "paper_2608_01718_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "dispatch_rules.cpp"), "-o", exe],
+                   check=True, capture_output=True)
+    return exe
+
+
+def test_dispatch_rules_take_the_faster_way(rules_checker):
+    """Where two ways of running a call were both timed, the rule between them takes the faster one."""
+    r = subprocess.run([rules_checker], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert r.stdout.startswith("ok ")
