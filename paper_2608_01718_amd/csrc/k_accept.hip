@@ -70,9 +70,9 @@ __device__ inline float load_one(const char* row, int dtype, int v) {
 // One workgroup per (query, position) row, grid-stride over the rows.  A row that does not start on a 16-byte
 // boundary (a vocabulary that is no multiple of 8) has its first elements taken one by one up to the next: 5120
 // rows of 128,257 bfloat16 logits take 211 us, as those of 128,256 do (205 us), and took 875 us one by one.
-// Workgroups of 256 threads where the rows fill the chip (5120 rows: 205 us, 222 us with 1024), of 1024 where a
-// row's own chain of loads is the bound: 1 to 20 rows of 128,256 logits 14 us against 22 us a call, 256 rows 20
-// against 41 us, 1024 rows 50 against 55 us; 512 rows of 32,000 float32 logits 17.4 against 16.2 us.
+// Workgroups of 256 threads where the rows fill the chip (5120 rows: 205 us, 222 us with 1024) or are short, of 1024
+// where a row's own chain of loads is the bound (accept_many_waves): 1 to 20 rows of 128,256 logits 14 us against
+// 22 us a call, 256 rows 20 against 41 us, 1024 rows 50 against 55 us.
 template <int kThreads>
 __global__ __launch_bounds__(kThreads) void k_token_prob(const void* __restrict__ logits, int dtype, int V,
                                                          const int32_t* __restrict__ tokens, int64_t rows,
@@ -156,8 +156,7 @@ hipError_t launch_accept_length(const void* logits, int dtype, int V, const int3
                                 int B, int k, int32_t* accept_len, float* p_target, hipStream_t s) {
     const int64_t rows = (int64_t)B * k;
     if (rows <= 0) return hipSuccess;
-    // few rows, or some of long ones: 16 waves on each
-    if (rows <= 256 || (rows <= 1024 && (int64_t)V * (dtype == 0 ? 4 : 2) >= 192 * 1024))
+    if (accept_many_waves(rows, V, dtype))
         k_token_prob<1024><<<dim3((unsigned)rows), dim3(1024), 0, s>>>(logits, dtype, V, tokens, rows, p_target);
     else
         k_token_prob<256><<<dim3((unsigned)grid_blocks(rows)), dim3(256), 0, s>>>(logits, dtype, V, tokens, rows,

@@ -173,6 +173,15 @@ hipError_t calibrate_static_scratch(uint32_t** out);
 
 // Speculative-decoding acceptance: p_target[b][j] = softmax(logits[b][j])[tokens[b][j]] (0 for an
 // out-of-range token); accept_len[b] = the number of leading positions with p_target >= p_draft.
+// Sixteen waves on each row of logits instead of four: few rows of many logits, where a row's own chain of loads is the
+// bound; short rows would only wait for the merge of waves that hold nothing, and more rows fill the chip with four
+// waves each.  Four / sixteen, us a call in a replayed graph: 100 rows of 1000, 8192 and 16,000 bfloat16 logits
+// 5.0 / 6.1, 6.5 / 6.7, 7.7 / 7.2, of 128,256 38 / 18; 256 rows of 1000, 8192, 16,000 and 100,003 float32 ones 5.2 / 6.2,
+// 5.9 / 7.3, 9.0 / 7.9, 24.3 / 22.6.  Beyond 256 rows float32 ones never gain (260 rows of 50,257 18.8 / 20.0, 512 of
+// 151,936 56.1 / 56.8); 512 rows of 100,003 bfloat16 ones take 38.9 / 23.5, of 8192 6.6 / 8.4.
+inline bool accept_many_waves(int64_t rows, int V, int dtype) {
+    return rows <= 256 ? V >= 12000 : rows <= 1024 && dtype == 1 && V >= 96 * 1024;
+}
 hipError_t launch_accept_length(const void* logits, int dtype, int V, const int32_t* tokens, const float* p_draft,
                                 int B, int k, int32_t* accept_len, float* p_target, hipStream_t s);
 

@@ -33,8 +33,25 @@ static void one_launch() {
               x.B, x.d_pad, x.resp);
 }
 
+// Acceptance with sixteen or four waves on a row, in a replayed graph: rows, logits a row, dtype (0 float32).
+static void accept() {
+    struct {
+        int rows, V, dtype;
+        double sixteen, four;
+    } t[] = {{1, 1000, 0, 5.50, 4.47},     {100, 1000, 1, 6.11, 5.02},   {256, 1001, 0, 6.42, 5.32},
+             {20, 8192, 0, 6.38, 5.31},    {256, 8192, 1, 6.92, 6.10},   {1, 16000, 1, 6.48, 7.09},
+             {256, 16000, 0, 7.86, 9.04},  {256, 32000, 1, 11.16, 15.01}, {100, 50257, 0, 10.24, 10.89},
+             {260, 50257, 0, 19.95, 18.80}, {512, 50257, 0, 23.79, 22.62}, {768, 1000, 1, 9.79, 5.83},
+             {512, 8192, 1, 8.38, 6.58},   {1000, 32000, 1, 23.20, 20.63}, {512, 100003, 1, 23.51, 38.85},
+             {1024, 151936, 1, 57.11, 69.11}, {1024, 32000, 0, 30.02, 26.31}};
+    for (auto& x : t)
+        check(accept_many_waves(x.rows, x.V, x.dtype), x.sixteen, x.four, "sixteen waves: rows, logits, dtype", x.rows,
+              x.V, x.dtype);
+}
+
 int main() {
     one_launch();
+    accept();
     if (failures) return 1;
     std::printf("ok dispatch rules\n");
     return 0;
