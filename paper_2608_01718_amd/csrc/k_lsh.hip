@@ -264,7 +264,7 @@ __device__ __forceinline__ uint32_t simhash_byte(X xat, const u32x4* __restrict_
     return sign_byte(lo, hi);
 }
 
-// Signatures of few rows (an insert of some hundred entries): one wave per (16-row group, signature byte of
+// Signatures of few rows (simhash_by_wave): one wave per (16-row group, signature byte of
 // every lane), so that the blocks of a group are computed in parallel.  Rows outside [row0, row0 + n) are not
 // written.  Grid-stride over the waves.
 __global__ __launch_bounds__(256) void k_simhash_few(const u32x4* __restrict__ rows_tiled, int kc, int64_t row0,
@@ -596,17 +596,11 @@ static void launch_bulk(const uint16_t* rows_tiled, int kc, int64_t row0, int64_
         (const u32x4*)rows_tiled, kc, row0, n, (const u32x4*)hp_tiled, n_tiles, (uint8_t*)sig);
 }
 
-// Rows per call up to which a wave per (16-row group, block pair) is used.  It spreads a call over the whole chip
-// but reads the hyperplanes once per group; a bulk call lasts at least one tile's chain (20 us at 768 columns).
-// Measured, few / bulk, us: 256 bits x 768 columns 8.2 / 20 at 4096 rows, 14 / 20 at 8192, 23 / 20 at 16384,
-// 112 / 31 at 65536; 128 bits x 1024 columns 6.9 / 24, 9.9 / 25, 16 / 24, 85 / 35.
-constexpr int64_t kFewRows = 8192;
-
 hipError_t launch_simhash(const uint16_t* rows_tiled, int d_pad, int64_t row0, int64_t n, const uint16_t* hp_tiled,
                           int bits, uint32_t* sig, int num_cu, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int words = bits >> 5, kc = d_pad >> 5;
-    if (n <= kFewRows) {
+    if (simhash_by_wave(n, bits)) {
         const int64_t groups = ((row0 + n + 15) >> 4) - (row0 >> 4);
         k_simhash_few<<<dim3((unsigned)grid_blocks((groups * words + 3) / 4)), dim3(256), 0, s>>>(
             (const u32x4*)rows_tiled, kc, row0, n, (const u32x4*)hp_tiled, words, (uint8_t*)sig);

@@ -190,6 +190,16 @@ hipError_t launch_accept_length(const void* logits, int dtype, int V, const int3
 // tiled matrix ([rows][bits / 32] words, bit i of a row is 1 when its projection on hyperplane i is >= 0),
 // and the whole LSH lookup of a query batch (query preparation, Hamming-radius candidate scan, exact re-rank,
 // threshold and stage 2).
+// Whether the signatures of n rows are computed a wave per (16-row group, signature byte) or by the bulk kernel.  The
+// first spreads a call over the whole chip but reads the hyperplanes once per group, so its time grows with rows x bits;
+// the second lasts at least one tile's chain, whatever the rows.  Both grow with the columns alike.  Few / bulk, us to
+// build an index of n rows in place: 64 bits x 2048 columns 28 / 39 at 12288 rows, 41 / 47 at 32768, 53 / 50 at 49152;
+// 128 bits x 1024 28 / 30 at 16384, 35 / 31 at 24576; 256 bits x 768 31 / 35 at 12288, 36 / 36 at 16384, 46 / 36 at
+// 24576; 256 x 2048 54 / 63, 66 / 63, 91 / 64; 32 bits x 384 20 / 21 at 49152, 22 / 22 at 65536.
+inline bool simhash_by_wave(int64_t n, int bits) {
+    const int64_t most = 2500000 / bits;
+    return n <= (most < 14000 ? 14000 : most);
+}
 hipError_t launch_tile_hyperplanes(const uint16_t* src, int bits, int d, int d_pad, uint16_t* dst, hipStream_t s);
 hipError_t launch_simhash(const uint16_t* rows_tiled, int d_pad, int64_t row0, int64_t n, const uint16_t* hp_tiled,
                           int bits, uint32_t* sig, int num_cu, hipStream_t s);

@@ -49,9 +49,25 @@ static void accept() {
               x.V, x.dtype);
 }
 
+// Signatures by a wave per group and byte or by the bulk kernel: rows, bits, columns.
+static void simhash() {
+    struct {
+        int n, bits, d;
+        double wave, bulk;
+    } t[] = {{8193, 64, 2048, 25.06, 38.49},   {8193, 128, 768, 22.29, 25.66},   {8193, 256, 2048, 46.30, 62.66},
+             {16384, 64, 1024, 21.40, 26.33},  {32768, 64, 2048, 41.10, 46.59},  {49152, 64, 768, 30.22, 27.60},
+             {49152, 32, 2048, 46.79, 48.72},  {12288, 128, 1024, 24.64, 29.11}, {24576, 128, 1024, 34.76, 30.92},
+             {24576, 128, 2048, 53.75, 47.69}, {12288, 192, 768, 28.82, 30.11},  {24576, 192, 384, 27.98, 24.66},
+             {12288, 256, 1536, 45.16, 52.03}, {24576, 256, 768, 45.75, 36.41},  {65536, 256, 2048, 228.55, 78.56},
+             {65536, 128, 768, 53.78, 35.54}};
+    for (auto& x : t)
+        check(simhash_by_wave(x.n, x.bits), x.wave, x.bulk, "signatures by wave: rows, bits, columns", x.n, x.bits, x.d);
+}
+
 int main() {
     one_launch();
     accept();
+    simhash();
     if (failures) return 1;
     std::printf("ok dispatch rules\n");
     return 0;
