@@ -201,12 +201,15 @@ def test_lsh_edges(lc):
 @pytest.mark.parametrize("bits", list(range(32, 257, 32)))
 def test_signatures_at_tile_edges(lc, bits):
     """Every signature width, on inserts whose rows start and end inside and at the edges of the signature
-    kernels' tiles (16-row groups, 256- and 512-row tiles, a single wave's rows), at both sides of the row count
-    where the bulk kernel takes over.  Away from EPS the bits equal the float64 signs; a query equal to a
+    kernels' tiles (16-row groups, 256-row tiles, a single wave's rows), at both sides of the row count where the bulk
+    kernel takes over, at aligned and unaligned first rows; and on the whole store, when the index is replaced by one
+    of the opposite hyperplanes (in the same buffers, whose old signatures differ from it in every bit but those of
+    zero projections) and by the first again.  Away from EPS the bits equal the float64 signs; a query equal to a
     stored row gets that row's signature (radius 0 finds it)."""
     import torch
-    for d, parts in ((100, (37, 4096, 1, 4097)), (700, (4097 + 511, 16, 5000)), (200, (4097, 255, 6000)),
-                     (60, (3 * 512 + 4096,))):
+    most = max(14000, 2500000 // bits)                # rows that a wave per group and byte takes
+    for d, parts in ((100, (37, most + 512, 1, 4097)), (700, (most, 16, 5000)), (200, (most + 1, 255, 6000)),
+                     (60, (3 * 512 + most,))):
         N = sum(parts)
         g = torch.Generator().manual_seed(bits * 1000 + d)
         keys = torch.randn((N, d), generator=g).to(torch.bfloat16).cuda()
@@ -219,15 +222,17 @@ def test_signatures_at_tile_edges(lc, bits):
         for n in parts:
             c.insert(keys[r0:r0 + n], keys[r0:r0 + n], tok[r0:r0 + n])
             r0 += n
-        ones = c.export_signatures(0, N).cpu()
-        c.enable_lsh(bits, hp, 8)                     # the whole store at once
-        assert torch.equal(ones, c.export_signatures(0, N).cpu())
-        z = c.export(0, N)[0].view(torch.bfloat16).double()
-        proj = (z @ hp.double().T).cpu().numpy()
-        got = np.unpackbits(ones.numpy().view(np.uint8), axis=-1, bitorder="little").astype(bool)
-        bad = (got != (proj >= 0)) & (np.abs(proj) >= EPS)
-        assert not bad.any(), (d, np.argwhere(bad)[:10])
-        assert got[N // 2].all()                      # a zero vector projects to zero, which counts as >= 0
+        ones = c.export_signatures(0, N)
+        c.enable_lsh(bits, -hp, 8)
+        opposite = c.export_signatures(0, N)
+        c.enable_lsh(bits, hp, 8)
+        assert torch.equal(ones, c.export_signatures(0, N))
+        proj = c.export(0, N)[0].view(torch.bfloat16).double() @ hp.double().T
+        for sig, p in ((ones, proj), (opposite, -proj)):
+            got = ((sig[..., None] >> torch.arange(32, device="cuda", dtype=torch.int32)) & 1).flatten(1).bool()
+            bad = (got != (p >= 0)) & (p.abs() >= EPS)
+            assert not bad.any(), (d, bad.nonzero()[:10])
+            assert got[N // 2].all()                  # a zero vector projects to zero, which counts as >= 0
         rows = torch.randint(N, (64,), generator=g).cuda()
         out = c.lookup_lsh(keys[rows], keys[rows], tok[rows], 0.9, 0.85, 1, 0)
         live = (rows != N // 2).cpu()
