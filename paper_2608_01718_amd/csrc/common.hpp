@@ -274,7 +274,7 @@ template <int NC>
 struct RawRow {
     u32x4 lo[NC], hi[NC];  // 16-byte pieces: lo alone for a chunk of bfloat16, both for one of float32
 };
-__device__ __forceinline__ bool row_is_chunked(const char* src, int d) {
+__host__ __device__ __forceinline__ bool row_is_chunked(const char* src, int d) {
     return ((uintptr_t)src & 15) == 0 && d % 8 == 0;
 }
 template <int NC, bool NT = false>
@@ -291,17 +291,7 @@ __device__ __forceinline__ void row_load(const char* src, int dtype, int d, bool
     for (int c = 0; c < NC; ++c) r.hi[c] = any && dtype == 0 ? at(c, 1) : u32x4{0u, 0u, 0u, 0u};
 }
 template <int NC>
-__device__ __forceinline__ void row_unpack(const char* src, int dtype, int d, bool live, int lane, const RawRow<NC>& r,
-                                           float (&x)[NC][8]) {
-    if (live && !row_is_chunked(src, d)) {
-        // The lane made opaque here: else the addresses and bounds of these elements are formed before the caller's
-        // loop over rows and hold 40 registers through it (the forms for 2048 columns spilled 84 to 176 bytes a lane:
-        // inserts of 4096 x 1536 float32 rows 26.6 us, 20.1 us so).
-        __asm__ volatile("" : "+v"(lane));
-#pragma unroll
-        for (int c = 0; c < NC; ++c) load8f(src, dtype, d, lane * 8 + 512 * c, x[c]);
-        return;
-    }
+__device__ __forceinline__ void row_unpack_chunks(int dtype, int d, int lane, const RawRow<NC>& r, float (&x)[NC][8]) {
     if (dtype == 0) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -324,6 +314,20 @@ __device__ __forceinline__ void row_unpack(const char* src, int dtype, int d, bo
             }
         }
     }
+}
+template <int NC>
+__device__ __forceinline__ void row_unpack(const char* src, int dtype, int d, bool live, int lane, const RawRow<NC>& r,
+                                           float (&x)[NC][8]) {
+    if (live && !row_is_chunked(src, d)) {
+        // The lane made opaque here: else the addresses and bounds of these elements are formed before the caller's
+        // loop over rows and hold 40 registers through it (the forms for 2048 columns spilled 84 to 176 bytes a lane:
+        // inserts of 4096 x 1536 float32 rows 26.6 us, 20.1 us so).
+        __asm__ volatile("" : "+v"(lane));
+#pragma unroll
+        for (int c = 0; c < NC; ++c) load8f(src, dtype, d, lane * 8 + 512 * c, x[c]);
+        return;
+    }
+    row_unpack_chunks<NC>(dtype, d, lane, r, x);
 }
 template <int NC>
 __device__ __forceinline__ void row_to_regs(const char* src, int dtype, int d, bool live, int lane, float (&x)[NC][8]) {

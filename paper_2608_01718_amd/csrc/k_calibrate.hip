@@ -13,6 +13,7 @@
 // 11 and 10 bits), each ended by a scan, in the workgroup that finishes last,
 // that fixes those bits of both ranks' keys (1M similarities: 12 + 9 + 9 us).
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -33,8 +34,12 @@ __constant__ const int kBits[kPasses] = {11, 11, 10};
 // lane keeps its 8 NC columns of both rows in registers, read once; the norms are summed in the order row_norm
 // uses, so the rounded values are those of the stored vectors.  Square root and reciprocal, 60 double-precision
 // operations that every lane needs of both norms, run once for the two (one norm in each half of the wave).
+// CHUNKED: both arrays have rows of whole aligned 16-byte chunks (row_is_chunked), loaded and rounded without branches;
+// else the rows are loaded chunk by chunk in turn and every element takes its own test for the division, in fewer
+// registers than rounding whole rows needs (100k pairs of 900 bfloat16 columns 218 us, 244 us in one kernel with the
+// chunked rows; of 1500 427 and 530 us).
 // NC = 0: any d, the rows read once for the norms and once for the dot.
-template <int NC>
+template <int NC, bool CHUNKED>
 __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const void* __restrict__ b, int dtype, int d,
                                             int64_t j, float* __restrict__ sims) {
     const int lane = threadIdx.x & 63;
@@ -44,11 +49,19 @@ __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const vo
     float acc = 0.0f;
     if constexpr (NC > 0) {
         float xa[NC][8], xb[NC][8];
-        RawRow<NC> wa, wb;  // non-temporal: each row is read once
-        row_load<NC, true>(ra, dtype, d, true, lane, wa);
-        row_load<NC, true>(rb, dtype, d, true, lane, wb);
-        row_unpack<NC>(ra, dtype, d, true, lane, wa, xa);
-        row_unpack<NC>(rb, dtype, d, true, lane, wb, xb);
+        if constexpr (CHUNKED) {
+            RawRow<NC> wa, wb;
+            row_load<NC, true>(ra, dtype, d, true, lane, wa);
+            row_load<NC, true>(rb, dtype, d, true, lane, wb);
+            row_unpack_chunks<NC>(dtype, d, lane, wa, xa);
+            row_unpack_chunks<NC>(dtype, d, lane, wb, xb);
+        } else {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                load8f(ra, dtype, d, lane * 8 + 512 * c, xa[c]);
+                load8f(rb, dtype, d, lane * 8 + 512 * c, xb[c]);
+            }
+        }
         double sa = 0.0, sb = 0.0;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -58,20 +71,32 @@ __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const vo
                 sb += (double)xb[c][e] * (double)xb[c][e];
             }
         sa = wave_sum_f64(sa), sb = wave_sum_f64(sb);
-        const double n = __builtin_sqrt(lane < 32 ? sa : sb);
-        const float rnf = quotient_rcp_f32(n);
-        const double na = __shfl(n, 0, kWave), nb = __shfl(n, 32, kWave);
-        const float rna = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rnf), 0));
-        const float rnb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rnf), 32));
-        if (__ballot(n == 0.0) == 0ull) {  // a zero vector normalises to zero and scores 0
-            uint32_t pa[NC * 4], pb[NC * 4];
-            quantise_row<NC>(xa, na, rna, d, lane, pa);
-            quantise_row<NC>(xb, nb, rnb, d, lane, pb);
+        if constexpr (CHUNKED) {
+            const double n = __builtin_sqrt(lane < 32 ? sa : sb);
+            const float rnf = quotient_rcp_f32(n);
+            const double na = __shfl(n, 0, kWave), nb = __shfl(n, 32, kWave);
+            const float rna = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rnf), 0));
+            const float rnb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rnf), 32));
+            if (__ballot(n == 0.0) == 0ull) {  // a zero vector normalises to zero and scores 0
+                uint32_t pa[NC * 4], pb[NC * 4];
+                quantise_row<NC>(xa, na, rna, d, lane, pa);
+                quantise_row<NC>(xb, nb, rnb, d, lane, pb);
 #pragma unroll
-            for (int k = 0; k < NC * 4; ++k) {
-                acc += __uint_as_float(pa[k] << 16) * __uint_as_float(pb[k] << 16);
-                acc += __uint_as_float(pa[k] & 0xFFFF0000u) * __uint_as_float(pb[k] & 0xFFFF0000u);
+                for (int k = 0; k < NC * 4; ++k) {
+                    acc += __uint_as_float(pa[k] << 16) * __uint_as_float(pb[k] << 16);
+                    acc += __uint_as_float(pa[k] & 0xFFFF0000u) * __uint_as_float(pb[k] & 0xFFFF0000u);
+                }
             }
+        } else if (sa != 0.0 && sb != 0.0) {
+            const double na = __builtin_sqrt(sa), nb = __builtin_sqrt(sb);
+            const float rna = quotient_rcp_f32(na), rnb = quotient_rcp_f32(nb);
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (lane * 8 + 512 * c + e >= d) continue;
+                    acc += bf16_rne_quotient_f32(xa[c][e], na, rna) * bf16_rne_quotient_f32(xb[c][e], nb, rnb);
+                }
         }
     } else {
         const double na = row_norm(ra, dtype, d, true, lane);
@@ -106,7 +131,7 @@ __device__ inline void select_init(uint32_t* state, uint32_t* hist, uint32_t r0,
 // carried state costs registers, and with them occupancy).
 // Bound by the vector ALU beside HBM.  1M pairs of 1024 bfloat16 columns: 710 us (5.8 TB/s), 945 us with the rounding
 // test and its division branch at every element, both norms in every lane and loads that waited for each other.
-template <int NC, bool LOOP>
+template <int NC, bool LOOP, bool CHUNKED>
 __global__ __launch_bounds__(256) void k_pair_cosine(const void* __restrict__ a, const void* __restrict__ b,
                                                      int dtype, int d, int64_t n, float* __restrict__ sims,
                                                      uint32_t* __restrict__ state, uint32_t* __restrict__ hist,
@@ -114,10 +139,10 @@ __global__ __launch_bounds__(256) void k_pair_cosine(const void* __restrict__ a,
     if (blockIdx.x == 0) select_init(state, hist, r0, r1);
     const int64_t j0 = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (LOOP) {
-        for (int64_t j = j0; j < n; j += (int64_t)gridDim.x * 4) pair_cosine<NC>(a, b, dtype, d, j, sims);
+        for (int64_t j = j0; j < n; j += (int64_t)gridDim.x * 4) pair_cosine<NC, CHUNKED>(a, b, dtype, d, j, sims);
     } else {
         if (j0 >= n) return;
-        pair_cosine<NC>(a, b, dtype, d, j0, sims);
+        pair_cosine<NC, CHUNKED>(a, b, dtype, d, j0, sims);
     }
 }
 
@@ -315,18 +340,25 @@ hipError_t launch_calibrate(const void* a, const void* b, int dtype, int d, int6
     uint32_t* hist = scratch + 64;
     const dim3 grid((unsigned)grid_blocks((n + 3) / 4)), block(256);
     const bool loop = (n + 3) / 4 > kMaxGridBlocks;
-    auto pairs = [&](auto looped, auto single) {
-        (loop ? looped : single)<<<grid, block, 0, s>>>(a, b, dtype, d, n, sims, state, hist, (uint32_t)lo,
-                                                        (uint32_t)hi);
+    const bool chunked = row_is_chunked((const char*)a, d) && row_is_chunked((const char*)b, d);
+    auto pairs = [&](auto kernel) {
+        kernel<<<grid, block, 0, s>>>(a, b, dtype, d, n, sims, state, hist, (uint32_t)lo, (uint32_t)hi);
+    };
+    auto columns = [&](auto nc) {
+        constexpr int NC = decltype(nc)::value;
+        if (chunked)
+            pairs(loop ? k_pair_cosine<NC, true, true> : k_pair_cosine<NC, false, true>);
+        else
+            pairs(loop ? k_pair_cosine<NC, true, false> : k_pair_cosine<NC, false, false>);
     };
     if (d <= 512)
-        pairs(k_pair_cosine<1, true>, k_pair_cosine<1, false>);
+        columns(std::integral_constant<int, 1>{});
     else if (d <= 1024)
-        pairs(k_pair_cosine<2, true>, k_pair_cosine<2, false>);
+        columns(std::integral_constant<int, 2>{});
     else if (d <= 2048)
-        pairs(k_pair_cosine<4, true>, k_pair_cosine<4, false>);
+        columns(std::integral_constant<int, 4>{});
     else
-        pairs(k_pair_cosine<0, true>, k_pair_cosine<0, false>);
+        pairs(loop ? k_pair_cosine<0, true, false> : k_pair_cosine<0, false, false>);
     if (n <= kSelectFew) {
         k_select_few<<<dim3(1), dim3(kSelectThreads), 0, s>>>(sims, n, (uint32_t)lo, (uint32_t)hi, frac, cap, tau);
         return hipGetLastError();

@@ -66,3 +66,14 @@ def test_kernels_need_no_scratch():
     assert len(kernels) > 40, sorted(kernels)
     limit = lambda name: max([v for k, v in ALLOWED.items() if name.startswith(k)], default=0)  # noqa: E731
     assert {k: v for k, v in kernels.items() if v > limit(k)} == {}
+
+
+def test_calibration_of_unaligned_rows_keeps_its_waves():
+    """Eight waves on a SIMD (64 registers) up to 1024 columns: with fewer the loads of rows that are no whole chunks
+    are waited for (72 registers: 245 us for 100k pairs of 900 bfloat16 columns, 218 us with at most 64)."""
+    with open(LIB, "rb") as f:
+        blob = f.read()
+    registers = {_name(k[".name"]): k[".vgpr_count"] for obj in _code_objects(blob)
+                 for k in _metadata(obj)["amdhsa.kernels"]}
+    for name in ("k_pair_cosine<1, 0, 0>", "k_pair_cosine<2, 0, 0>"):
+        assert registers[name] <= 64, (name, registers[name])
