@@ -51,8 +51,19 @@ __device__ __forceinline__ void pair_cosine(const void* __restrict__ a, const vo
         float xa[NC][8], xb[NC][8];
         if constexpr (CHUNKED) {
             RawRow<NC> wa, wb;
-            row_load<NC, true>(ra, dtype, d, true, lane, wa);
-            row_load<NC, true>(rb, dtype, d, true, lane, wb);
+            // Non-temporally, as each row is read once; but not float32 rows of more than one chunk per lane: a lane's two
+            // pieces of a chunk are loaded one after the other, so every line is asked for twice (100k pairs of 2048
+            // float32 columns 370 us, 300 us with plain loads, of 1024 174 and 168 us; of 2048 bfloat16 ones 167 and
+            // 173 us).
+            if (NC == 1 || dtype != 0) {
+                int ln = lane;
+                if constexpr (NC > 1) __asm__ volatile("" : "+v"(ln));  // else both branches' loads become plain ones
+                row_load<NC, true>(ra, dtype, d, true, ln, wa);
+                row_load<NC, true>(rb, dtype, d, true, ln, wb);
+            } else {
+                row_load<NC>(ra, dtype, d, true, lane, wa);
+                row_load<NC>(rb, dtype, d, true, lane, wb);
+            }
             row_unpack_chunks<NC>(dtype, d, lane, wa, xa);
             row_unpack_chunks<NC>(dtype, d, lane, wb, xb);
         } else {
