@@ -38,19 +38,17 @@
 // count (zero padding, which must never win) occur only in the last tile of
 // the last range and are masked there.  At the end each workgroup writes one
 // packed candidate per query.
-#include <initializer_list>
 #include <type_traits>
 
 #include "common.hpp"
-#include "launch.hpp"
+#include "gemm_shape.hpp"
 
 namespace lacache {
 
 namespace {
 
 constexpr int kWK = 4;                 // waves per workgroup, one 128-key slice each
-constexpr int kMaxKB = 8;              // most 16-row key blocks per wave (KB of the kernel)
-constexpr int kMinKB = 5;              // fewest
+constexpr int kMaxKB = kGemmMaxKB;     // most 16-row key blocks per wave (KB of the kernel)
 constexpr int kQB = 8;                 // 16-query blocks per wave (all waves share them)
 constexpr int kTQ = kQB * 16;          // queries per workgroup tile
 constexpr int kS = 2;                  // 32-column steps per LDS stage of the query tile
@@ -310,66 +308,18 @@ hipError_t launch_stage1_gemm(const uint16_t* keys, const uint16_t* qt, int B, i
                               int num_cu, int* P_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const int kc = d_pad / 32;
     if (n_rows <= 0 || B <= 0 || kc % kU != 0) return hipErrorInvalidValue;
-    const int n_qtiles = (B + kTQ - 1) / kTQ;
-    // XCD placement: the fewest query groups (1, 2, 4 or 8) whose query tiles fit one XCD's L2 beside the key
-    // stream, at most 3 MiB per XCD (a count of tiles that does not divide evenly: all in one group up to 4.5 MiB);
-    // plain round-robin (0) when the counts allow none
-    auto placement = [&](int ranges) {
-        for (int x = 1; x <= 8; x *= 2)
-            if (n_qtiles % x == 0 && ranges % (8 / x) == 0 &&
-                (int64_t)(n_qtiles / x) * kTQ * d_pad * 2 <= (int64_t(3) << 20))
-                return x;
-        return ranges % 8 == 0 && (int64_t)n_qtiles * kTQ * d_pad * 2 <= (int64_t(9) << 19) ? 1 : 0;
-    };
-    // Key ranges and tile height, by the time of the longest workgroup in key blocks.  A CU holds one workgroup (each
-    // wave has a SIMD's whole register file), so what counts is rounds of workgroups x tiles of a range x rows of a
-    // tile, and:
-    // - one workgroup more than the CUs costs a whole round: 2200 queries (18 query tiles) on 1M x 768 keys in 15
-    //   ranges took 4.97 ms, 2.69 ms in 14; several rounds are weighed too, they fill the last one better;
-    // - without a placement the workgroups of a range sit on several XCDs, each fetching its keys; with few query
-    //   tiles that is slower than the contraction.  300 queries (3 tiles) on 200k x 768 keys in 86 ranges (both
-    //   faults) took 200 us, 113 us in 80; 600 (5 tiles) on 500k x 768 818 and 427 us;
-    // - a range of few tiles wastes much of its last one, which a lower tile avoids (64 rows per block, 8 blocks at
-    //   most; half a block per tile for the loop, 7 % more per row of a lower tile, which feeds fewer products per
-    //   query fragment): 256 queries on 100k x 1024 keys, 782 rows per range, two tiles of 448 rows 60.6 us, of
-    //   512 64.3 us; on 50k x 384, one of 448 rows 16.3 us, of 512 20.7 us.
-    const int scattered = n_qtiles == 1 ? 100 : n_qtiles < 12 ? 160 : n_qtiles < 24 ? 112 : 103;  // percent
-    int kb = kMaxKB, n_ktiles = 0, n_ranges = 0, xq = 0;
-    int64_t least = INT64_MAX;
-    for (int x = kMaxKB; x >= kMinKB; --x) {
-        const int tiles = (n_rows + kWK * x * 16 - 1) / (kWK * x * 16);
-        for (int rounds = 1; rounds <= 3; ++rounds) {
-            const int fill = rounds * num_cu / n_qtiles, most = fill < 1 ? 1 : fill < tiles ? fill : tiles;
-            for (int mask : {0, 1, 3, 7}) {
-                const int ranges = most & ~mask;
-                if (ranges < 1) continue;
-                const int place = placement(ranges);
-                const int64_t turns = ((int64_t)ranges * n_qtiles + num_cu - 1) / num_cu;
-                const int64_t cost = turns * ((tiles + ranges - 1) / ranges) * (2 * x + 1) * (x == kMaxKB ? 100 : 107) *
-                                     (place > 0 ? 100 : scattered);
-                if (cost < least) kb = x, n_ktiles = tiles, n_ranges = ranges, xq = place, least = cost;
-            }
-        }
-    }
-    if (n_ranges > kMaxPartials) n_ranges = kMaxPartials, xq = placement(n_ranges);
-    // the key offsets of a range stay below 2^31 bytes (its tiles plus the prefetch overrun)
-    const int64_t tile_bytes = (int64_t)kWK * kb * 16 * d_pad * 2;
-    const int64_t max_tiles = ((int64_t(1) << 31) - 1) / tile_bytes - 1;
-    if (max_tiles < 1) return hipErrorInvalidValue;
-    if ((n_ktiles + n_ranges - 1) / n_ranges > max_tiles) {
-        n_ranges = (int)((n_ktiles + max_tiles - 1) / max_tiles);
-        xq = placement(n_ranges);
-    }
-    if (n_ranges > kMaxPartials) return hipErrorInvalidValue;
-    *P_out = n_ranges;
+    const GemmShape g = gemm_shape(n_rows, B, d_pad, num_cu);
+    if (g.n_ranges < 1) return hipErrorInvalidValue;
+    *P_out = g.n_ranges;
     auto run = [&](auto kernel, std::atomic<uint64_t>& lds_done) {
         const hipError_t e = allow_dynamic_lds((const void*)kernel, kLds, lds_done);
         if (e != hipSuccess) return e;
-        return launch_timed(kernel, dim3(n_qtiles * n_ranges), dim3(kWK * 64), kLds, s, e0, e1, (const u32x4*)keys,
-                            (const u32x4*)qt, kc, n_rows, n_ktiles, n_qtiles, n_ranges, xq, B, n_ranges, part);
+        return launch_timed(kernel, dim3(g.n_qtiles * g.n_ranges), dim3(kWK * 64), kLds, s, e0, e1, (const u32x4*)keys,
+                            (const u32x4*)qt, kc, n_rows, g.n_ktiles, g.n_qtiles, g.n_ranges, g.xq, B, g.n_ranges,
+                            part);
     };
     static std::atomic<uint64_t> lds_done[kMaxKB + 1] = {};
-    switch (kb) {
+    switch (g.kb) {
         case 5: return run(k_stage1_gemm<5>, lds_done[5]);
         case 6: return run(k_stage1_gemm<6>, lds_done[6]);
         case 7: return run(k_stage1_gemm<7>, lds_done[7]);
