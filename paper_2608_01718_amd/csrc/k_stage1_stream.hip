@@ -17,6 +17,7 @@
 // (best score, index) per query in registers; rows are visited in increasing
 // order and only a strictly larger score replaces the best, so the lowest
 // index wins ties.
+#include "done_slots.hpp"
 #include "verify.hpp"
 
 namespace lacache {
@@ -35,7 +36,7 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
                                                         const void* __restrict__ qraw, int dtype, int d, int kc,
                                                         int groups, int n_rows, int n_ranges, int n_qgroups, int B,
                                                         uint64_t* __restrict__ part, uint32_t* __restrict__ done,
-                                                        const VerifyArgs v) {
+                                                        uint32_t* __restrict__ done_next, const VerifyArgs v) {
     extern __shared__ u32x4 smem[];
     u32x4* qs = smem;                                        // [QG][kc][64] query fragments
     uint64_t* red = (uint64_t*)(smem + QG * kc * 64);        // [kStreamWaves][QG * 16]
@@ -172,17 +173,10 @@ __global__ __launch_bounds__(1024) void k_stage1_stream(const u32x4* __restrict_
         last_workgroup_wait();
         __syncthreads();
         uint32_t* const last = (uint32_t*)red;
-        if (tid == 0) {
-            // counted by XCD first (dispatch is round-robin over the 8): 256 additions to one word would queue up
-            const uint32_t x = blockIdx.x & 7u, of_x = (gridDim.x - x + 7u) / 8u, xs = gridDim.x < 8u ? gridDim.x : 8u;
-            bool l = atomicAdd(&done[(1 + x) * 32], 1u) == of_x - 1;
-            if (l) {
-                done[(1 + x) * 32] = 0u;
-                l = atomicAdd(&done[0], 1u) == xs - 1;
-                if (l) done[0] = 0u;
-            }
-            *last = l ? 1u : 0u;
-        }
+        if (tid == 0)
+            *last = count_done(done, blockIdx.x, gridDim.x, [](uint32_t* p) { return atomicAdd(p, 1u); }) ? 1u : 0u;
+        if (blockIdx.x == 0 && tid < kDoneCount)
+            __hip_atomic_store(&done_next[tid * kDoneStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (*last == 0u) return;
         if (wid < B) {
@@ -296,6 +290,7 @@ struct StreamLaunch {
     hipEvent_t e0, e1;
     const VerifyArgs* verify;
     uint32_t* done;
+    uint32_t ticket;
 };
 
 template <int QG, bool NT, int NCQ>
@@ -306,7 +301,8 @@ static hipError_t launch_qgn(const StreamLaunch& a) {
     if (e != hipSuccess) return e;
     return launch_timed(k_stage1_stream<QG, NT, NCQ>, dim3(a.n_ranges * a.n_qgroups), dim3(kStreamWaves * 64), lds,
                         a.s, a.e0, a.e1, a.keys, a.qt, a.qraw, a.dtype, a.d, a.kc, a.groups, a.n_rows, a.n_ranges,
-                        a.n_qgroups, a.B, a.part, a.verify ? a.done : nullptr, a.verify ? *a.verify : VerifyArgs{});
+                        a.n_qgroups, a.B, a.part, a.verify ? done_slot(a.done, a.ticket) : nullptr,
+                        a.verify ? done_slot(a.done, a.ticket + 1) : nullptr, a.verify ? *a.verify : VerifyArgs{});
 }
 
 // ncq: 0 reads the staged queries, 1 / 2 / 4 normalises the caller's rows in the kernel (d_pad <= 512 * ncq)
@@ -334,7 +330,8 @@ int stream_max_qg(int d_pad) {
 
 hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B, int n_rows, int d_pad,
                                 uint64_t* part, int num_cu, int* P_out, hipStream_t s, hipEvent_t e0, hipEvent_t e1,
-                                const void* qraw, int dtype, int d, const VerifyArgs* verify, uint32_t* done) {
+                                const void* qraw, int dtype, int d, const VerifyArgs* verify, uint32_t* done,
+                                uint32_t ticket) {
     const int kc = d_pad / 32;
     const int ncq = qraw == nullptr ? 0 : stream_fused_ncq(d_pad);
     if (verify != nullptr && (B > 16 || !stream_ends_lookup(1, ncq) || done == nullptr)) return hipErrorInvalidValue;
@@ -360,7 +357,7 @@ hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B,
     if (n_ranges < 1) n_ranges = 1;
     *P_out = n_ranges;
     const StreamLaunch a{(const u32x4*)keys, (const u32x4*)qt, qraw, dtype, d, ncq, kc, groups, n_rows,
-                         n_ranges, n_qgroups, B, part, s, e0, e1, verify, done};
+                         n_ranges, n_qgroups, B, part, s, e0, e1, verify, done, ticket};
     const bool single = n_qgroups == 1;
     switch (qg) {
         case 1: return single ? launch_qg<1, true>(a) : launch_qg<1, false>(a);

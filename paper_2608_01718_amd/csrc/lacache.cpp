@@ -9,6 +9,7 @@
 #include <utility>
 #include <vector>
 
+#include "done_slots.hpp"
 #include "launch.hpp"
 
 namespace lacache {
@@ -47,8 +48,9 @@ struct lacache_s {
     uint64_t* part = nullptr;  // [max_batch][kMaxPartials] packed top-1 candidates
     uint32_t* calib = nullptr; // [kCalibScratchWords] state and histograms of the calibration select
     uint32_t* fallbacks = nullptr;  // [1] queries whose stage-1 group replay missed its score (see k_verify.hip)
-    uint32_t* done = nullptr;  // [kDoneWords] counts of finished workgroups of the streaming kernel, zero between
-                               // calls (the second part of the allocation of `fallbacks`)
+    uint32_t* done = nullptr;  // [kDoneWords] counts of finished workgroups of the streaming kernel (the second part
+                               // of the allocation of `fallbacks`)
+    uint32_t done_ticket = 0;  // launches so far that counted there
     // LSH index (lacache_enable_lsh): hyperplanes, key and query signatures, candidate lists
     int lsh_bits = 0, lsh_max_cand = 0;
     uint16_t* hp = nullptr;        // tiled [lsh_bits][d_pad] raw hyperplanes
@@ -136,6 +138,16 @@ EntryArrays store_arrays(lacache_s* h) {
     a.tokens = h->tokens;
     a.k_cap = h->k_cap;
     return a;
+}
+
+// Whether the stream is being captured into a graph.  A captured launch would count in the same slot at every replay,
+// which no launch before it clears, so captured lookups end in a launch of their own (as fast there: a launch costs
+// little in a replay).
+bool is_captured(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 void clear_prof(lacache_s* h) { h->prof_used = 0; }
@@ -306,7 +318,7 @@ static int lookup_chunk(lacache_t h, const char* queries, int B, const VerifyArg
         const bool fused = small && B <= 32 && stream_fused_ncq(h->d_pad) > 0;
         int64_t resp_columns = 0;
         for (int i = 0; i < v.models.m; ++i) resp_columns += v.models.d_pad[i];
-        const bool whole = fused && lookup_in_one_launch(B, n_rows, h->d_pad, resp_columns);
+        const bool whole = fused && lookup_in_one_launch(B, n_rows, h->d_pad, resp_columns) && !is_captured(s);
         if (!fused && launch_normalise(queries, h->dtype, B, rows_pad, h->d, h->d_pad, h->qt, 0, true, s) != hipSuccess)
             return LACACHE_EHIP;
         hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -323,11 +335,14 @@ static int lookup_chunk(lacache_t h, const char* queries, int B, const VerifyArg
             e = launch_stage1_wide(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s, e0, e1);
         else if (small)
             e = launch_stage1_stream(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s, e0, e1,
-                                     fused ? queries : nullptr, h->dtype, h->d, whole ? &v : nullptr, h->done);
+                                     fused ? queries : nullptr, h->dtype, h->d, whole ? &v : nullptr, h->done, h->done_ticket);
         else
             e = launch_stage1_gemm(h->keys, h->qt, B, n_rows, h->d_pad, h->part, h->num_cu, &P, s, e0, e1);
         if (e != hipSuccess) return LACACHE_EHIP;
-        if (whole) return LACACHE_OK;
+        if (whole) {
+            ++h->done_ticket;  // a launch that failed has cleared no slot
+            return LACACHE_OK;
+        }
     }
     if (launch_finalize_verify(h->part, P, !small, h->keys, h->qt, B, n_rows, h->dtype, h->d, v, h->fallbacks, s) !=
         hipSuccess)

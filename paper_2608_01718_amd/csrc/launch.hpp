@@ -109,13 +109,12 @@ struct VerifyArgs {
 // With events e0 / e1 the kernel's run time is recorded into them (launch_timed).  With qraw (the caller's
 // [B][d] query rows, dtype 0 f32 / 1 bf16) the kernel normalises the queries itself and qt is not read; this
 // takes d_pad <= 2048 (stream_fused_ncq(d_pad) > 0) and B <= 32.  With `verify` too (lookup_in_one_launch) the
-// workgroup that ends last also merges the partials and runs stage 2, so no launch follows;
-// done: kDoneWords words, zero between launches (the kernel leaves them so).
-constexpr int kDoneWords = 9 * 32;
+// workgroup that ends last also merges the partials and runs stage 2, so no launch follows; it counts in the slot of
+// `ticket` in done (done_slots.hpp: the caller gives every launch the ticket after the last one's).
 hipError_t launch_stage1_stream(const uint16_t* keys, const uint16_t* qt, int B, int n_rows, int d_pad,
                                 uint64_t* part, int num_cu, int* P_out, hipStream_t s, hipEvent_t e0 = nullptr,
                                 hipEvent_t e1 = nullptr, const void* qraw = nullptr, int dtype = 0, int d = 0,
-                                const VerifyArgs* verify = nullptr, uint32_t* done = nullptr);
+                                const VerifyArgs* verify = nullptr, uint32_t* done = nullptr, uint32_t ticket = 0);
 int stream_fused_ncq(int d_pad);
 // Whether a lookup of B queries (d_pad columns) on n_rows entries, its prefix models of resp_columns padded columns in
 // all, ends in its streaming launch.  That saves a launch, but one workgroup then does what the launch spreads over

@@ -589,6 +589,45 @@ def test_lookup_graph_capture_and_replay(lc):
     c.close()
 
 
+@pytest.mark.parametrize("B", [1, 8])
+def test_small_lookups_captured_and_direct(lc, B):
+    """Small lookups, which end in their streaming launch when called directly and in a launch of their own when
+    captured: 20 replays of a graph of two, each between direct calls (more of them in all than there are slots to
+    count their workgroups in), agree with the GEMM path bit for bit."""
+    import torch
+    g = torch.Generator().manual_seed(B)
+    keys = torch.randn((10_000, 384), generator=g).cuda()
+    tok = torch.randint(50, (10_000, 5), generator=g, dtype=torch.int32).cuda()
+    c = lc.LaCache(10_000, 384, 5, lc.F32, 64, 0)
+    c.insert(keys, keys, tok)
+    q, t = keys[:B].clone(), tok[:B].clone()
+    outs = [c.lookup(q, q, t, 0.9, 0.85, 5) for _ in range(2)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for o in outs:
+            c.lookup(q, q, t, 0.9, 0.85, 5, out=o)
+    for rep in range(20):
+        rows = torch.randint(10_000, (B,), generator=g).cuda()
+        q.copy_(keys[rows] + 0.01 * rep)
+        t.copy_(tok[rows])
+        for o in outs:
+            for x in o:
+                x.fill_(-7)
+        got = [c.lookup(q, q, t, 0.9, 0.85, 5)]
+        graph.replay()
+        got += outs + [c.lookup(q, q, t, 0.9, 0.85, 5)]
+        c.set_small_batch(0)
+        want = c.lookup(q, q, t, 0.9, 0.85, 5)
+        c.set_small_batch(-1)
+        for o in got:
+            for a, b in zip(o, want):
+                assert torch.equal(a.view(torch.int32), b.view(torch.int32)), (rep, a, b)
+    torch.cuda.synchronize()
+    graph.reset()
+    c.close()
+
+
 def test_interleaved_inserts(lc):
     """A query planted near an entry is a miss before that entry is inserted and a hit after it."""
     sp = synth.spec("large", N=12_288, B=256)

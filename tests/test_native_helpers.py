@@ -67,3 +67,16 @@ def test_dispatch_rules_take_the_faster_way(rules_checker):
     r = subprocess.run([rules_checker], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
     assert r.stdout.startswith("ok ")
+
+
+def test_workgroup_counts_start_from_zero(tmp_path):
+    """A launch finds its last workgroup whatever launches overlapped by mistake before it."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path / "done_slots")
+    subprocess.run([HIPCC, "-O2", "-std=c++17", "--offload-arch=gfx950",
+                    "-I", os.path.join(ROOT, "paper_2608_01718_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "done_slots.cpp"), "-o", exe], check=True, capture_output=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert r.stdout.startswith("ok ")
