@@ -306,7 +306,13 @@ int lacache_export_signatures(lacache_t h, int64_t first, int32_t n, uint32_t *s
 int lacache_set_small_batch(lacache_t h, int32_t b_small);
 
 /*
- * Timing of the stage-1 kernel.  With every = n > 0, the 1st, (n+1)-th,
+ * Timing of the stage-1 kernel.  The time of a launch is that kernel's from
+ * start to end, which holds other parts of a lookup too: the normalisation of
+ * the queries up to 32 queries of d <= 2048; and, where the lookup is that one
+ * launch, the merge of the candidates, the threshold and stage 2 (up to 8
+ * queries, 16 on stores of n * d_pad <= 2^23, of d <= 1024, if queries times
+ * the padded columns of all prefix models are at most 12288, outside a stream
+ * capture).  With every = n > 0, the 1st, (n+1)-th,
  * (2n+1)-th ... stage-1 launch from now on (one per lookup, or per chunk of
  * max_batch queries) is timed: the launch goes through hipExtLaunchKernel
  * with a HIP event pair that takes the kernel's own start and end times, on
