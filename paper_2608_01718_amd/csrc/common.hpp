@@ -205,11 +205,16 @@ __device__ inline uint64_t wave_max_u64(uint64_t x) { return wave_reduce(x, umax
 // ---------------------------------------------------------------------------
 // "The last workgroup to finish goes on": every workgroup publishes its part with device-wide atomic
 // operations only, calls this, and after a workgroup barrier one thread adds 1 to a counter; the workgroup
-// that counts last reads the parts with device-wide atomic loads.  Atomic operations take effect where all
-// XCDs see them, and the wait returns when this wave's have: they are ordered before the counter without
-// writing the XCD's L2 back, as a device-wide release fence does (25 us per pass of 256 workgroups).
+// that counts last reads the parts with device-wide atomic loads.  The order rests on gfx950, not on the language's
+// memory model, in which relaxed operations order nothing between workgroups: there, device-wide atomic operations take
+// effect where all XCDs see them, and s_waitcnt returns when this wave's have, so they come before the counter.  It
+// holds only for words that are written and read by device-wide atomics alone.  A device-wide release fence in
+// its place writes the XCD's L2 back (25 us per pass of 256 workgroups).  Not for another target without a look at it.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void last_workgroup_wait() {
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "last_workgroup_wait orders atomics as gfx950 does; use __threadfence() elsewhere"
+#endif
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);
 }
