@@ -108,6 +108,20 @@ __host__ __device__ inline uint16_t bf16_rne_quotient(float v, double n, float r
     return (uint16_t)(u >> 16);
 }
 
+// The lane index computed afresh (not kept live across a main loop whose registers are all in use).
+__device__ inline int fresh_lane() {
+    int r;
+    __asm__ volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(r));
+    return r;
+}
+
+// Workgroup barrier that orders LDS accesses only: loads from memory stay in flight across it.
+__device__ inline void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // Elements j0 .. j0+7 of a row as floats (0 beyond d; bfloat16 widens exactly): one or two 16-byte loads when
@@ -358,7 +372,10 @@ __device__ __forceinline__ double regs_norm(const float (&x)[NC][8]) {
 // does not cover (within 2 units of a rounding midpoint, or below 2^-125) goes through the division for it.
 // One element in 13,000 is such a one, 7 % of 1024-column rows hold any, so the test is made once per row and
 // the loop over a lane's elements is left out of the common path (with a branch per element, bulk inserts of
-// 1024-column prefix rows stored 131,000 of them in 79 us; 65 us so).  A zero norm gives zeros.  The whole wave
+// 1024-column prefix rows stored 131,000 of them in 79 us; 65 us so).  Rows with zeros (exact as they are, but below
+// 2^-125), and last chunks that d does not fill, always go through that loop's first half: inserts of 20,000 x 1024
+// bfloat16 entries 45 us, 52 us where half of the elements are zero (48 and 58 us with a branch per element).  A zero norm
+// gives zeros.  The whole wave
 // calls it, with one n for all lanes; rnf = quotient_rcp_f32(n).
 template <int NC>
 __device__ __forceinline__ void quantise_row(const float (&x)[NC][8], double n, float rnf, int d, int lane,

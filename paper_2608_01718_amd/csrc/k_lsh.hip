@@ -28,13 +28,6 @@ namespace lacache {
 // signature bytes in order and stores them without any exchange.
 // ---------------------------------------------------------------------------
 
-// The lane index computed afresh (not kept live across a main loop whose registers are all in use).
-__device__ inline int fresh_lane() {
-    int r;
-    __asm__ volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(r));
-    return r;
-}
-
 // f(0), f(1), ... with compile-time indices.
 template <int... Q, class F>
 __device__ __forceinline__ void for_each_index(std::integer_sequence<int, Q...>, F f) {
@@ -145,12 +138,6 @@ __global__ __launch_bounds__(256, HB <= 6 ? 2 : 1) void k_simhash_bulk(const u32
 #pragma unroll
         for (int hb = 0; hb < kHP; ++hb) dst[hb] = ring[(slot * kSlot + s * HB + p * kHP + hb) * 64 + lane];
     };
-    auto barrier = [&]() {  // orders LDS accesses only: loads from memory stay in flight across it
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
-
     f32x4 acc[kRB][HB];
 #pragma unroll
     for (int p = 0; p < SETS - 1; ++p) rows_load(kf[p]);
@@ -159,7 +146,7 @@ __global__ __launch_bounds__(256, HB <= 6 ? 2 : 1) void k_simhash_bulk(const u32
     slot_load();
     slot_store(1);
     slot_load();
-    barrier();
+    lds_barrier();
     frags(0, 0, 0, hf[0]);
 
     // one part of a step: load the rows SETS - 1 steps ahead, read the next part's fragments, multiply set u (the
@@ -168,7 +155,7 @@ __global__ __launch_bounds__(256, HB <= 6 ? 2 : 1) void k_simhash_bulk(const u32
         constexpr int q = decltype(q_tag)::value, u = q / PARTS, p = q % PARTS;
         constexpr int v = (q + 1) % (SETS * PARTS), vu = v / PARTS % 4;  // the next part, its step
         if constexpr (u % 2 == 1 && p == PARTS - 1) {
-            barrier();
+            lds_barrier();
             slot_store(u / 2 % 2);
             slot_load();
         }

@@ -71,20 +71,6 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7FFFFFFF, 0x00020000);
 }
 
-// The lane index computed afresh (not kept live across the main loop, whose registers are all in use).
-__device__ inline int fresh_lane() {
-    int r;
-    __asm__ volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(r));
-    return r;
-}
-
-// Workgroup barrier that orders LDS accesses only: outstanding global loads are not waited for.
-__device__ inline void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 }  // namespace
 
 // Workgroup -> (query tile, key range): with xq > 0 the 8 XCDs (dispatch is round-robin over them) form xq

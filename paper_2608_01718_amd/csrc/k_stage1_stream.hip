@@ -227,11 +227,6 @@ __global__ __launch_bounds__(512, 2) void k_stage1_wide(const u32x4* __restrict_
 #pragma unroll
         for (int i = 0; i < kLoads; ++i) smem[(slot * kG * KC + wv + 8 * i) * 64 + lane] = src[i];
     };
-    auto barrier = [&]() {  // orders LDS accesses only: the fetches stay in flight across it
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
 #pragma unroll
     for (int t = 0; t < SETS; ++t) fetch(set[t], s0 + t);
     u32x4 qf[KC];
@@ -242,7 +237,7 @@ __global__ __launch_bounds__(512, 2) void k_stage1_wide(const u32x4* __restrict_
     int bidx = 0x7FFFFFFF;
     publish(0, set[0]);
     fetch(set[0], s0 + SETS);
-    barrier();
+    lds_barrier();
     for (int t = s0; t < s1; t += kUnroll) {
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -269,7 +264,7 @@ __global__ __launch_bounds__(512, 2) void k_stage1_wide(const u32x4* __restrict_
                     }
                 }
             }
-            barrier();
+            lds_barrier();
         }
     }
     uint64_t p = bidx == 0x7FFFFFFF ? 0ull : pack_top1(best, bidx);
