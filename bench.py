@@ -76,9 +76,9 @@ def parse():
 
 STAGE1_KERNELS = {"serve_large": "k_stage1_gemm", "serve_small": "k_stage1_stream<1, true, 2>",
                   "large": "k_stage1_gemm"}
-STAGE1_SOURCES = {"serve_large": ["k_stage1_gemm.hip", "common.hpp"],
-                  "serve_small": ["k_stage1_stream.hip", "verify.hpp", "common.hpp"],
-                  "large": ["k_stage1_gemm.hip", "common.hpp"]}
+STAGE1_SOURCES = {"serve_large": ["k_stage1_gemm.hip", "gemm_shape.hpp", "common.hpp"],
+                  "serve_small": ["k_stage1_stream.hip", "verify.hpp", "done_slots.hpp", "common.hpp"],
+                  "large": ["k_stage1_gemm.hip", "gemm_shape.hpp", "common.hpp"]}
 # the counter runs each workload's figures come from: serve_large and serve_small share one bench run,
 # the 4M x 1024 schedule has a run of its own (it launches the same GEMM kernel)
 PMC_RUNS = {"serve_large": "bench", "serve_small": "bench", "large": "large"}
