@@ -173,11 +173,11 @@ hipError_t calibrate_static_scratch(uint32_t** out);
 // Speculative-decoding acceptance: p_target[b][j] = softmax(logits[b][j])[tokens[b][j]] (0 for an
 // out-of-range token); accept_len[b] = the number of leading positions with p_target >= p_draft.
 // Sixteen waves on each row of logits instead of four: few rows of many logits, where a row's own chain of loads is the
-// bound; short rows would only wait for the merge of waves that hold nothing, and more rows fill the chip with four
-// waves each.  Four / sixteen, us a call in a replayed graph: 100 rows of 1000, 8192 and 16,000 bfloat16 logits
-// 5.0 / 6.1, 6.5 / 6.7, 7.7 / 7.2, of 128,256 38 / 18; 256 rows of 1000, 8192, 16,000 and 100,003 float32 ones 5.2 / 6.2,
-// 5.9 / 7.3, 9.0 / 7.9, 24.3 / 22.6.  Beyond 256 rows float32 ones never gain (260 rows of 50,257 18.8 / 20.0, 512 of
-// 151,936 56.1 / 56.8); 512 rows of 100,003 bfloat16 ones take 38.9 / 23.5, of 8192 6.6 / 8.4.
+// bound; more rows fill the chip with four waves each, and in short ones most of the sixteen hold nothing.  Four /
+// sixteen, us a call in a replayed graph: 256 rows of 1000, 4000 and 8192 float32 logits 5.1 / 5.1, 5.6 / 5.9, 6.3 / 6.1,
+// of 12,000, 16,000 and 100,003 7.1 / 6.3, 9.2 / 6.9, 25.7 / 23.5; 100 rows of 12,000, 32,000 and 128,256 bfloat16 ones
+// 6.1 / 5.5, 12.1 / 9.3, 38 / 17.  Beyond 256 rows float32 ones hardly gain (260 rows of 50,257 18.9 / 19.2, 512 of 151,936
+// 58.5 / 58.4); 512 rows of 100,003 bfloat16 ones take 38.9 / 22.1, of 8192 6.4 / 7.0, 2048 of 128,256 88 / 95.
 inline bool accept_many_waves(int64_t rows, int V, int dtype) {
     return rows <= 256 ? V >= 12000 : rows <= 1024 && dtype == 1 && V >= 96 * 1024;
 }

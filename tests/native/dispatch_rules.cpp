@@ -38,12 +38,12 @@ static void accept() {
     struct {
         int rows, V, dtype;
         double sixteen, four;
-    } t[] = {{1, 1000, 0, 5.50, 4.47},     {100, 1000, 1, 6.11, 5.02},   {256, 1001, 0, 6.42, 5.32},
-             {20, 8192, 0, 6.38, 5.31},    {256, 8192, 1, 6.92, 6.10},   {1, 16000, 1, 6.48, 7.09},
-             {256, 16000, 0, 7.86, 9.04},  {256, 32000, 1, 11.16, 15.01}, {100, 50257, 0, 10.24, 10.89},
-             {260, 50257, 0, 19.95, 18.80}, {512, 50257, 0, 23.79, 22.62}, {768, 1000, 1, 9.79, 5.83},
-             {512, 8192, 1, 8.38, 6.58},   {1000, 32000, 1, 23.20, 20.63}, {512, 100003, 1, 23.51, 38.85},
-             {1024, 151936, 1, 57.11, 69.11}, {1024, 32000, 0, 30.02, 26.31}};
+    } t[] = {{256, 4000, 0, 5.87, 5.62},    {256, 12000, 0, 6.25, 7.14},  {1, 12000, 1, 5.03, 5.69},
+             {100, 12000, 1, 5.46, 6.12},   {1, 16000, 1, 5.46, 6.97},    {256, 16000, 0, 6.88, 9.18},
+             {256, 32000, 1, 10.01, 14.86}, {100, 50257, 0, 9.31, 12.31}, {256, 100003, 0, 23.54, 25.69},
+             {1024, 8192, 0, 10.18, 8.62},  {512, 1000, 0, 5.66, 5.24},   {512, 8192, 1, 7.03, 6.41},
+             {1000, 32000, 0, 27.56, 26.30}, {2048, 128256, 1, 95.03, 88.11}, {1000, 8192, 1, 10.16, 8.04},
+             {512, 100003, 1, 22.09, 38.89}, {1024, 151936, 1, 55.79, 68.80}, {1024, 32000, 0, 28.14, 26.77}};
     for (auto& x : t)
         check(accept_many_waves(x.rows, x.V, x.dtype), x.sixteen, x.four, "sixteen waves: rows, logits, dtype", x.rows,
               x.V, x.dtype);

@@ -148,3 +148,23 @@ def test_acceptance_row_alignment_and_counts(lc, f32):
             assert err.numel() == 0 or err.max() <= 2e-5, (B, k, V, shift, err.max())
             assert torch.all(p[want == 0] == 0)
             assert torch.equal(n, (p >= pd).int().cumprod(1).sum(1).int())
+
+
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+@pytest.mark.parametrize("V", [12000, 16000, 20003, 32001])
+def test_target_probabilities_within_a_rounding(lc, V, dtype):
+    """Few rows, which sixteen waves share: the root mean square of the relative error of P_f against 64 bits stays
+    below the unit roundoff of float32, 2^-24, over 1920 rows (four waves on a row reach 1.03 to 1.13 of it, the
+    sixteen merged one after another 1.22 to 1.35)."""
+    import torch
+    g = torch.Generator().manual_seed(V)
+    total, rows = 0.0, 160
+    for scale in (1, 2, 3) * 4:
+        logits = (torch.randn((rows, 1, V), generator=g) * scale).to(getattr(torch, dtype)).cuda()
+        tok = torch.randint(V, (rows, 1), generator=g, dtype=torch.int32).cuda()
+        _, p = lc.lacache_accept_length(logits, tok, torch.zeros((rows, 1), device="cuda"))
+        want = torch.softmax(logits[:, 0].double(), 1).gather(1, tok.long())
+        total += float((((p.double() - want) / want) ** 2).sum())
+    rms = (total / (12 * rows)) ** 0.5
+    say(f"[ok] V={V} {dtype}: {rms:.3e}")
+    assert rms < 2.0 ** -24
