@@ -174,10 +174,11 @@ hipError_t calibrate_static_scratch(uint32_t** out);
 // out-of-range token); accept_len[b] = the number of leading positions with p_target >= p_draft.
 // Sixteen waves on each row of logits instead of four: few rows of many logits, where a row's own chain of loads is the
 // bound; more rows fill the chip with four waves each, and in short ones most of the sixteen hold nothing.  Four /
-// sixteen, us a call in a replayed graph: 256 rows of 1000, 4000 and 8192 float32 logits 5.1 / 5.1, 5.6 / 5.9, 6.3 / 6.1,
-// of 12,000, 16,000 and 100,003 7.1 / 6.3, 9.2 / 6.9, 25.7 / 23.5; 100 rows of 12,000, 32,000 and 128,256 bfloat16 ones
-// 6.1 / 5.5, 12.1 / 9.3, 38 / 17.  Beyond 256 rows float32 ones hardly gain (260 rows of 50,257 18.9 / 19.2, 512 of 151,936
-// 58.5 / 58.4); 512 rows of 100,003 bfloat16 ones take 38.9 / 22.1, of 8192 6.4 / 7.0, 2048 of 128,256 88 / 95.
+// sixteen, us a call in a replayed graph: 256 rows of 1000, 4000 and 8192 float32 logits 5.1 / 5.1, 5.6 / 5.9,
+// 6.3 / 6.1, of 12,000, 16,000 and 100,003 7.1 / 6.3, 9.2 / 6.9, 25.7 / 23.5; 100 rows of 12,000, 32,000 and 128,256
+// bfloat16 ones 6.1 / 5.5, 12.1 / 9.3, 38 / 17.  Beyond 256 rows float32 ones hardly gain (260 rows of 50,257
+// 18.9 / 19.2, 512 of 151,936 58.5 / 58.4); 512 rows of 100,003 bfloat16 ones take 38.9 / 22.1, of 8192 6.4 / 7.0, 2048
+// of 128,256 88 / 95.
 inline bool accept_many_waves(int64_t rows, int V, int dtype) {
     return rows <= 256 ? V >= 12000 : rows <= 1024 && dtype == 1 && V >= 96 * 1024;
 }
